@@ -1613,7 +1613,8 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
       const auto ok = std::make_tuple(c.lpp, c.apl, block, int((lds_l + 255) / 256));
       auto oi = occ.find(ok);
       if (oi == occ.end())
-        oi = occ.emplace(ok, sample_max_blocks_per_cu(c.lpp, c.apl, block, r->mode, (lds_l + 255) / 256 * 256)).first;
+        oi = occ.emplace(ok, sample_max_blocks_per_cu(c.lpp, c.apl, block, r->mode, p->local_opt, p->record_trace != 0,
+                                                         (lds_l + 255) / 256 * 256)).first;
       per_cu = oi->second;
     }
     auto key = std::make_tuple(c.lpp, c.apl, block, per_cu);
@@ -1687,7 +1688,8 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
       B.n_items = int(items.size()) - B.item_off;
       const size_t lds = sample_lds_bytes(B.lpp, B.apl, B.block, B.max_pairs);
       if (lds > 64 * 1024) return bail(DOCK_E_LIMIT, "pair list too long for the LDS budget");
-      const int per_cu = sample_max_blocks_per_cu(B.lpp, B.apl, B.block, r->mode, lds);
+      const int per_cu = sample_max_blocks_per_cu(B.lpp, B.apl, B.block, r->mode, p->local_opt,
+                                                  p->record_trace != 0, lds);
       B.grid = std::min(B.n_items, per_cu * n_cu);
       B.per_cu = per_cu;
     }

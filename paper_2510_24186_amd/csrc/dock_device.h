@@ -418,13 +418,19 @@ struct Trilerp {
   float fx, fy, fz;  // cell fractions
 };
 
+// FUSED: the fraction in one rounding, else from the rounded cell
+// coordinate.  Written out (y and z fused, x not) so that every kernel and
+// every WANT of eval_pose places a point in its cell with the same bits,
+// however the compiler splits the blocks around it.
+template <bool FUSED>
 DK_INLINE void cell_axis(float p, float o, float hi, float inv_h, int n, float& pc, bool& in, int& c,
                          float& f) {
+#pragma clang fp contract(off)
   pc = __builtin_amdgcn_fmed3f(p, o, hi);  // clamp to [o, hi]
   in = pc == p;
   const float u = (pc - o) * inv_h;        // >= 0, so truncation is floor
   c = min(int(u), n - 2);
-  f = u - float(c);
+  f = FUSED ? __builtin_fmaf(pc - o, inv_h, -float(c)) : u - float(c);
 }
 
 DK_INLINE Trilerp trilerp(const float* __restrict__ M, const GridDev& g, float px, float py, float pz) {
@@ -432,9 +438,9 @@ DK_INLINE Trilerp trilerp(const float* __restrict__ M, const GridDev& g, float p
   float pcx, pcy, pcz;
   bool ix, iy, iz;
   int cx, cy, cz;
-  cell_axis(px, g.origin[0], g.hi[0], g.inv_spacing, g.dims[0], pcx, ix, cx, t.fx);
-  cell_axis(py, g.origin[1], g.hi[1], g.inv_spacing, g.dims[1], pcy, iy, cy, t.fy);
-  cell_axis(pz, g.origin[2], g.hi[2], g.inv_spacing, g.dims[2], pcz, iz, cz, t.fz);
+  cell_axis<false>(px, g.origin[0], g.hi[0], g.inv_spacing, g.dims[0], pcx, ix, cx, t.fx);
+  cell_axis<true>(py, g.origin[1], g.hi[1], g.inv_spacing, g.dims[1], pcy, iy, cy, t.fy);
+  cell_axis<true>(pz, g.origin[2], g.hi[2], g.inv_spacing, g.dims[2], pcz, iz, cz, t.fz);
   // nodes per map <= 2^30: 32-bit node indices
   const uint32_t nx = uint32_t(g.dims[0]), nxy = uint32_t(g.dims[0]) * uint32_t(g.dims[1]);
   t.base = int((uint32_t(cz) * uint32_t(g.dims[1]) + uint32_t(cy)) * nx + uint32_t(cx));
@@ -1036,13 +1042,19 @@ DK_INLINE void gather_forces(const uint2& pw, uint32_t fb_a, float (&fsum)[APL][
 // E_MDN term when mdn.par is set.
 // MODE: 0 receptor terms from the grid maps, 1 summed pair by pair over the
 // receptor cell list, 2 grid maps plus the E_MDN term.
+// WANT: the energy, the gradient or both.  What is not wanted is neither
+// computed nor exchanged (no force store and gather, chain rule or scans for
+// the energy alone; no logarithms, map values or energy sum for the gradient
+// alone); what is comes out bit for bit as with both.
 constexpr int kModeGrid = 0, kModeDirect = 1, kModeGridMdn = 2;
+constexpr int kWantE = 1, kWantG = 2, kWantBoth = 3;
 
-template <int LPP, int APL, bool WANT_X = false, int MODE = kModeGrid>
+template <int LPP, int APL, int WANT = kWantBoth, bool WANT_X = false, int MODE = kModeGrid>
 DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& pk,
                             const PairRec* __restrict__ pairs, const GroupSlab& S, int r,
                             float (*xo)[3] = nullptr, float (*go)[3] = nullptr,
                             const MdnArg& mdn = MdnArg{nullptr, 0, 0}) {
+  constexpr bool WE = (WANT & kWantE) != 0, WG = (WANT & kWantG) != 0;
   LaneLig<APL> L = Lin;
   launder(L);
   // ---- atoms: place, interpolate, publish coordinates to the slab
@@ -1092,7 +1104,7 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
     // padding entry the host stages after the pull bytes) and is unused.
     const int cap = L.pull_cap;
     const uint32_t xs_a = lds_addr(S.xs), fb_a = lds_addr(S.fb);
-    if (r == 0) {
+    if (WG && r == 0) {
       // a zero produced here, not a zero tuple kept live (and spilled)
       // across the sampler's loops
       float z = 0.f;
@@ -1113,6 +1125,28 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
       uint32_t rec_a = recs_a + 16u * lane_slot, pw_a = pulls_a + kPullBytes * lane_slot;
       const uint32_t rec_step = 16u * uint32_t(W), pw_step = kPullBytes * uint32_t(W);
       uint4 rp = lds_read_u4(rec_a);
+      if (!WG) {
+        // the energy alone: nothing is exchanged between the passes, so the
+        // record is read two passes ahead and its positions one, and neither
+        // latency is waited for
+        f32x4_t xi = lds_read4(lds_entry16<0>(rp.x, xs_a));
+        f32x4_t xj = lds_read4(lds_entry16<1>(rp.x, xs_a));
+        if (L.n_pass > 1) rec_a += rec_step;
+        uint4 rp1 = lds_read_u4(rec_a);
+        for (int ps = 0; ps < L.n_pass; ++ps) {
+          if (ps + 2 < L.n_pass) rec_a += rec_step;
+          const f32x4_t yi = lds_read4(lds_entry16<0>(rp1.x, xs_a)), yj = lds_read4(lds_entry16<1>(rp1.x, xs_a));
+          const uint4 rp2 = lds_read_u4(rec_a);
+          float f[3];
+          const float e = pair_force_slot(L, rp, xi, xj, f);
+          if (slot_lane) e_lane += e;
+          rp = rp1;
+          rp1 = rp2;
+          xi = yi;
+          xj = yj;
+        }
+        return;
+      }
       uint2 pw = lds_read_u2(pw_a);
       f32x4_t xi = lds_read4(lds_entry16<0>(rp.x, xs_a));
       f32x4_t xj = lds_read4(lds_entry16<1>(rp.x, xs_a));
@@ -1124,7 +1158,7 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
         float f[3];
         const float e = pair_force_slot(L, rp, xi, xj, f);
         if (slot_lane) {
-          e_lane += e;
+          if (WE) e_lane += e;
           lds_write4(fb_a + 16u * uint32_t(r), f[0], f[1], f[2]);
         }
         if (ps + 1 < L.n_pass) {
@@ -1145,8 +1179,11 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
         wave_sync();
       }
     };
-    // caps: 4 or 8 with one atom per lane, 2 or 4 with two
-    if (APL == 2 && cap == 2)
+    // caps: 4 or 8 with one atom per lane, 2 or 4 with two (the energy alone
+    // gathers nothing: any cap's loop)
+    if (!WG)
+      run_passes(std::integral_constant<int, 4>{});
+    else if (APL == 2 && cap == 2)
       run_passes(std::integral_constant<int, 2>{});
     else if (APL == 2 || cap == 4)
       run_passes(std::integral_constant<int, 4>{});
@@ -1154,13 +1191,15 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
       run_passes(std::integral_constant<int, 8>{});
   } else {
     // ---- strided: lane r takes records r, r + LPP, ...; forces by LDS atomics
+    if (WG) {
 #pragma unroll
-    for (int s = 0; s < APL; ++s) {
-      const int atom = APL * r + s;
-      if (atom < L.n_atoms) {
-        S.fx[atom] = 0.0;
-        S.fy[atom] = 0.0;
-        S.fz[atom] = 0.0;
+      for (int s = 0; s < APL; ++s) {
+        const int atom = APL * r + s;
+        if (atom < L.n_atoms) {
+          S.fx[atom] = 0.0;
+          S.fy[atom] = 0.0;
+          S.fz[atom] = 0.0;
+        }
       }
     }
     wave_sync();
@@ -1173,8 +1212,9 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
       const int i = pr.w & 0xff, j = (pr.w >> 8) & 0xff;
       float f[3];
       const f32x4_t xi = lds_read4(lds_addr(S.xs + i)), xj = lds_read4(lds_addr(S.xs + j));
-      e_lane += pair_force(L, pr, make_float4(xi.x, xi.y, xi.z, 0.f), make_float4(xj.x, xj.y, xj.z, 0.f), f);
-      if (f[0] != 0.f || f[1] != 0.f || f[2] != 0.f) {
+      const float e = pair_force(L, pr, make_float4(xi.x, xi.y, xi.z, 0.f), make_float4(xj.x, xj.y, xj.z, 0.f), f);
+      if (WE) e_lane += e;
+      if (WG && (f[0] != 0.f || f[1] != 0.f || f[2] != 0.f)) {
         atomicAdd(&S.fx[i], double(f[0]));
         atomicAdd(&S.fy[i], double(f[1]));
         atomicAdd(&S.fz[i], double(f[2]));
@@ -1187,7 +1227,7 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
 #pragma unroll
     for (int s = 0; s < APL; ++s) {
       const int atom = APL * r + s;
-      if (atom < L.n_atoms) {
+      if (WG && atom < L.n_atoms) {
         fsum[s][0] = float(S.fx[atom]);
         fsum[s][1] = float(S.fy[atom]);
         fsum[s][2] = float(S.fz[atom]);
@@ -1208,9 +1248,9 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
       go[s][0] = g[s][0]; go[s][1] = g[s][1]; go[s][2] = g[s][2];
     }
   }
-  EvalOut out;
-  out.E = group_sum<LPP>(e_lane);
-  out.g = chain_rule<LPP, APL>(L, rg, x, g, S, r);
+  EvalOut out{0.f, 0.f};
+  if (WE) out.E = group_sum<LPP>(e_lane);
+  if (WG) out.g = chain_rule<LPP, APL>(L, rg, x, g, S, r);
   wave_sync();  // slab reuse by the next evaluation
   return out;
 }

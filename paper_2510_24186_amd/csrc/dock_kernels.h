@@ -184,6 +184,6 @@ hipError_t launch_philox(const uint32_t* ctr, uint32_t k0, uint32_t k1, long lon
 hipError_t launch_fill_int(int* p, int n, int v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, long long n, uint32_t v, hipStream_t s);
 hipError_t launch_add_int(int* p, int v, hipStream_t s);
-int sample_max_blocks_per_cu(int lpp, int apl, int block, int mode, size_t lds);
+int sample_max_blocks_per_cu(int lpp, int apl, int block, int mode, int local_opt, bool trace, size_t lds);
 
 }  // namespace dock

@@ -289,7 +289,7 @@ __global__ void __launch_bounds__(64) score_kernel(ScoreArgs a) {
   wave_sync();
   const float q = r < lg.n_dof ? a.q[pose * a.q_stride + r] : 0.f;
   float xo[APL][3], go[APL][3];
-  const EvalOut o = eval_pose<LPP, APL, true, MODE>(L, q, pk, gp, S, r, xo, go, mdn_for(a.L, lg, pk));
+  const EvalOut o = eval_pose<LPP, APL, kWantBoth, true, MODE>(L, q, pk, gp, S, r, xo, go, mdn_for(a.L, lg, pk));
   if (r == 0) a.E[pose] = o.E;
   if (a.dEdq && r < lg.n_dof) a.dEdq[pose * a.q_stride + r] = o.g;
   if (a.xyz) {
@@ -557,7 +557,12 @@ DK_INLINE float wrap_clamp(float q, int r, const LaneLig<APL>& L) {
   return wrap_angle(q);
 }
 
-template <int LPP, int APL, int MODE>
+// FULL: line search and logged trajectories, where every evaluation gives E
+// and the gradient.  Otherwise the first-order rules use the energy of a
+// step's last evaluation only and no gradient there, so the n_local
+// evaluations before it compute the gradient alone and that one (like the
+// initial pose's) the energy alone.
+template <int LPP, int APL, int MODE, bool FULL>
 DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const PocketDev& pk, const MdnArg& mdn,
                         const PairRec* pairs,
                         const GroupSlab& S, int lig, int traj, int r) {
@@ -567,7 +572,7 @@ DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const Pocket
   const int qs = a.q_stride;
   int nev = a.n_evals[ti];
   float* trow = nullptr;
-  if (a.trace && lig % a.trace_stride == 0 && traj < a.trace_traj)
+  if (FULL && a.trace && lig % a.trace_stride == 0 && traj < a.trace_traj)
     trow = a.trace + (size_t(lig / a.trace_stride) * a.trace_traj + traj) * size_t(a.trace_cap) * (2 * qs + 1);
   auto record = [&](float qv, float gv, float Ev) {
     if (trow && nev < a.trace_cap) {
@@ -583,7 +588,8 @@ DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const Pocket
   if (a.init) {
     const uint4 w = philox4x32_10(make_uint4(uint32_t(traj), 0u, 0u, uint32_t(r >> 2)), k0, k1);
     const float q = dof ? L.lo + (L.hi - L.lo) * u01(pick4(w, r & 3)) : 0.f;
-    const EvalOut o = eval_pose<LPP, APL, false, MODE>(L, q, pk, pairs, S, r, nullptr, nullptr, mdn);
+    const EvalOut o =
+        eval_pose<LPP, APL, FULL ? kWantBoth : kWantE, false, MODE>(L, q, pk, pairs, S, r, nullptr, nullptr, mdn);
     record(q, o.g, o.E);
     if (dof) {
       a.q_cur[ti * qs + r] = q;
@@ -606,16 +612,23 @@ DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const Pocket
     float qn = q;
     if (r == j) qn = L.lo + (L.hi - L.lo) * u01(w.y);
     float E;
-    if (a.local_opt != DOCK_LOCAL_LINESEARCH) {
+    if (!FULL || a.local_opt != DOCK_LOCAL_LINESEARCH) {
       // n_local gradient evaluations with a first-order update after each
       // (Adam by default; the Table S5 alternatives otherwise), then the
-      // energy of the refined pose: one evaluation site, n_local + 1 calls
+      // energy of the refined pose (FULL: one evaluation site, n_local + 1
+      // calls)
       float m = 0.f, v = 0.f, b1t = 1.f, b2t = 1.f;
       for (int t = 0;; ++t) {
-        const EvalOut o = eval_pose<LPP, APL, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn);
+        if (!FULL && t == a.n_local) {
+          E = eval_pose<LPP, APL, kWantE, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn).E;
+          record(qn, 0.f, E);
+          break;
+        }
+        const EvalOut o =
+            eval_pose<LPP, APL, FULL ? kWantBoth : kWantG, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn);
         record(qn, o.g, o.E);
         E = o.E;
-        if (t == a.n_local) break;
+        if (FULL && t == a.n_local) break;
         const float g = o.g;
         // square roots and quotients on the hardware units (about 1 ulp;
         // the IEEE-exact sequences cost ~12 instructions each)
@@ -650,7 +663,7 @@ DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const Pocket
       bool first = true;
       E = 0.f;
       for (;;) {
-        const EvalOut o = eval_pose<LPP, APL, false, MODE>(L, qtry, pk, pairs, S, r, nullptr, nullptr, mdn);
+        const EvalOut o = eval_pose<LPP, APL, kWantBoth, false, MODE>(L, qtry, pk, pairs, S, r, nullptr, nullptr, mdn);
         record(qtry, o.g, o.E);
         if (first) {
           E = o.E;
@@ -702,7 +715,7 @@ DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const Pocket
 // Three waves per SIMD (168 VGPRs).  With two atoms per lane the step loop
 // needs more and spills a few registers to scratch (served from L2, outside
 // the pair-pass loop); two waves per SIMD without spills measured slower.
-template <int LPP, int APL, int BLOCK, int MODE>
+template <int LPP, int APL, int BLOCK, int MODE, bool FULL>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) sample_kernel(SampleArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int GPB = BLOCK / LPP;
@@ -755,16 +768,23 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3)))
       const PocketDev pk = a.pockets[lg.pocket];
       LaneLig<APL> L;
       load_lane_lig<LPP, APL>(L, lg, a.L.ligs + lig, a.L.atoms, a.L.frags, a.L.tors, pk, r);
-      run_traj<LPP, APL, MODE>(a, L, pk, mdn_for(a.L, lg, pk), sp, S, lig, traj, r);
+      run_traj<LPP, APL, MODE, FULL>(a, L, pk, mdn_for(a.L, lg, pk), sp, S, lig, traj, r);
     }
     __syncthreads();
   }
 }
 
+// Runs that log trajectories or search along a line evaluate E and the
+// gradient every time.
+static bool full_evals(int local_opt, bool trace) { return trace || local_opt == DOCK_LOCAL_LINESEARCH; }
+
 template <int LPP, int APL, int BLOCK, int MODE>
 static hipError_t launch_sample_t(const SampleArgs& a, int grid, hipStream_t s) {
   const size_t lds = sample_lds_bytes(LPP, APL, BLOCK, a.max_pairs);
-  hipLaunchKernelGGL((sample_kernel<LPP, APL, BLOCK, MODE>), dim3(grid), dim3(BLOCK), lds, s, a);
+  if (full_evals(a.local_opt, a.trace != nullptr))
+    hipLaunchKernelGGL((sample_kernel<LPP, APL, BLOCK, MODE, true>), dim3(grid), dim3(BLOCK), lds, s, a);
+  else
+    hipLaunchKernelGGL((sample_kernel<LPP, APL, BLOCK, MODE, false>), dim3(grid), dim3(BLOCK), lds, s, a);
   return hipGetLastError();
 }
 
@@ -787,23 +807,25 @@ hipError_t launch_sample(const SampleArgs& a, int lpp, int apl, int grid, int bl
   return hipErrorInvalidValue;
 }
 
-template <int L, int A, int B>
+template <int L, int A, int B, bool FULL>
 static int blocks_per_cu(int mode, size_t lds) {
   int n = 0;
   hipError_t e;
   if (mode == kModeDirect)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sample_kernel<L, A, B, kModeDirect>, B, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sample_kernel<L, A, B, kModeDirect, FULL>, B, lds);
   else if (mode == kModeGridMdn)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sample_kernel<L, A, B, kModeGridMdn>, B, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sample_kernel<L, A, B, kModeGridMdn, FULL>, B, lds);
   else
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sample_kernel<L, A, B, kModeGrid>, B, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sample_kernel<L, A, B, kModeGrid, FULL>, B, lds);
   if (e != hipSuccess) n = 1;
   return n > 0 ? n : 1;
 }
 
-int sample_max_blocks_per_cu(int lpp, int apl, int block, int mode, size_t lds) {
-#define X(L, A, B) \
-  if (lpp == L && apl == A && block == B) return blocks_per_cu<L, A, B>(mode, lds);
+int sample_max_blocks_per_cu(int lpp, int apl, int block, int mode, int local_opt, bool trace, size_t lds) {
+  const bool full = full_evals(local_opt, trace);
+#define X(L, A, B)                              \
+  if (lpp == L && apl == A && block == B)       \
+    return full ? blocks_per_cu<L, A, B, true>(mode, lds) : blocks_per_cu<L, A, B, false>(mode, lds);
   DOCK_SAMPLE_CASES(X)
 #undef X
   return 1;
