@@ -13,6 +13,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <stdexcept>
 #include <string>
 #include <thread>
 #include <tuple>
@@ -620,6 +621,18 @@ static void pack_ligand(const LigandHost& H, const TypePair* tab, PackedLigand& 
     pi_new[p] = H.atom_new[H.pair_i[p]];
     pj_new[p] = H.atom_new[H.pair_j[p]];
   }
+  // the distinct clash distances' log2, and per type pair the byte offset of
+  // its entry (bits 16-23 of the pair word)
+  float clash_log2[kClashTable] = {};
+  uint32_t l2_byte[kTypes * kTypes];
+  int n_l2 = 0;
+  for (int t = 0; t < kTypes * kTypes; ++t) {
+    const float l2 = float(std::log2(double(tab[t].dclash)));
+    const int k = int(std::find(clash_log2, clash_log2 + n_l2, l2) - clash_log2);
+    if (k == kClashTable) throw std::logic_error("more clash distances than table entries");
+    if (k == n_l2) clash_log2[n_l2++] = l2;
+    l2_byte[t] = uint32_t(4 * k) << 16;
+  }
   auto record = [&](int i0, int j0) {
     PairRec pr{};
     if (i0 < 0) {
@@ -629,8 +642,7 @@ static void pack_ligand(const LigandHost& H, const TypePair* tab, PackedLigand& 
     }
     const int ti = H.type[H.dfs_atom[i0]], tj = H.type[H.dfs_atom[j0]];
     const TypePair& tp = tab[ti * kTypes + tj];
-    pr.w = uint32_t(i0) | (uint32_t(j0) << 8) | (uint32_t(ti) << 16) | (uint32_t(tj) << 20) |
-           (tp.flags << 24);
+    pr.w = uint32_t(i0) | (uint32_t(j0) << 8) | l2_byte[ti * kTypes + tj] | (tp.flags << 24);
     pr.rsum = tp.rsum;
     return pr;
   };
@@ -645,10 +657,10 @@ static void pack_ligand(const LigandHost& H, const TypePair* tab, PackedLigand& 
     lay.pair_off = int(pairs.size());
     PassPlan plan;
     if (!pi_new.empty()) plan = schedule_passes(H.n_atoms, pi_new, pj_new, lc.lpp, lc.apl);
-    // the pass layout stages 2 entries per slot and apl * cap pull bytes
-    // per lane and pass; with two atoms per lane above 64 atoms it is kept
-    // only where it fits the LDS budget
-    const size_t pull_bytes = size_t(plan.n_pass) * lc.lpp * lc.apl * plan.cap;
+    // with two atoms per lane above 64 atoms the pass layout is kept only
+    // where slots and pull bytes fit the LDS budget
+    const int per_lane = lc.apl * plan.cap;
+    const size_t pull_bytes = size_t(plan.n_pass) * lc.lpp * per_lane;
     const size_t pass_entries = plan.slot_i.size() * 2 + pull_bytes / sizeof(PairRec) + 1;
     if (plan.n_pass > 0 &&
         (H.n_atoms <= 64 || pass_entries * sizeof(PairRec) <= kPassStageBytes)) {
@@ -656,40 +668,48 @@ static void pack_ligand(const LigandHost& H, const TypePair* tab, PackedLigand& 
       lay.pass_w = lc.lpp;
       lay.pass_apl = lc.apl;
       lay.pull_cap = plan.cap;
-      // 16-byte slot records (pair word, radius sum, d_clash^2 as the
-      // device squares it, log2 d_clash), then the pull bytes
+      // pull bytes per (pass, lane): the lane's atoms one after the other,
+      // the first `cap` bytes of each atom's pull list (cap 4 or 8 with one
+      // atom per lane, 2 or 4 with two)
+      auto pull_word = [&](size_t slot, int word) {
+        const uint64_t* w = &plan.pulls[(slot / lc.lpp) * plan.n_pull + lc.apl * (slot % lc.lpp)];
+        if (lc.apl == 1) return uint32_t(w[0] >> (32 * word));
+        if (plan.cap == 4) return uint32_t(w[word]);
+        return uint32_t(w[0] & 0xffffu) | uint32_t(w[1] & 0xffffu) << 16;
+      };
+      // 16-byte slot records: pair word, radius sum, d_clash^2 as the device
+      // squares it (negated for a donor/acceptor pair: the kernel tests
+      // |d_clash^2| for the clash term and the sign for the hydrogen-bond
+      // term), first pull word
+      pairs.reserve(pairs.size() + plan.slot_i.size() * (per_lane == 8 ? 5 : 4) / 2 + kClashTable / 2);
       for (size_t s = 0; s < plan.slot_i.size(); ++s) {
         const int i0 = plan.slot_i[s], j0 = plan.slot_j[s];
         pairs.push_back(record(i0, j0));
         PairRec cl{};
         if (i0 >= 0) {
           const TypePair& tp = tab[H.type[H.dfs_atom[i0]] * kTypes + H.type[H.dfs_atom[j0]]];
-          // negated for a donor/acceptor pair: the kernel tests
-          // |d_clash^2| for the clash term and the sign for the
-          // hydrogen-bond term
           cl.w = bits((tp.flags & 1u) ? -tp.dclash2 : tp.dclash2);
-          cl.rsum = float(std::log2(double(tp.dclash)));
         }
+        const uint32_t w0 = pull_word(s, 0);
+        std::memcpy(&cl.rsum, &w0, 4);
         pairs.push_back(cl);
       }
-      // pull bytes per (pass, lane): the lane's atoms one after the other,
-      // the first `cap` bytes of each atom's pull list
-      std::vector<uint8_t> pb(pull_bytes);
-      const int per_lane = lc.apl * plan.cap;
-      for (int ps = 0; ps < plan.n_pass; ++ps)
-        for (int ln = 0; ln < lc.lpp; ++ln)
-          for (int sa = 0; sa < lc.apl; ++sa) {
-            const uint64_t w = plan.pulls[size_t(ps) * plan.n_pull + lc.apl * ln + sa];
-            for (int b = 0; b < plan.cap; ++b)
-              pb[(size_t(ps) * lc.lpp + ln) * per_lane + sa * plan.cap + b] = uint8_t(w >> (8 * b));
-          }
-      for (size_t o = 0; o < pb.size(); o += sizeof(PairRec)) {
+      // the second pull words, where a lane has eight bytes (a pass has an
+      // even number of lanes: whole entries)
+      if (per_lane == 8)
+        for (size_t s = 0; s < plan.slot_i.size(); s += 2) {
+          PairRec pw;
+          const uint32_t a = pull_word(s, 1), b = pull_word(s + 1, 1);
+          pw.w = a;
+          std::memcpy(&pw.rsum, &b, 4);
+          pairs.push_back(pw);
+        }
+      for (int k = 0; k < kClashTable; k += 2) {
         PairRec pw;
-        std::memcpy(&pw, pb.data() + o, sizeof(PairRec));
+        pw.w = bits(clash_log2[k]);
+        pw.rsum = clash_log2[k + 1];
         pairs.push_back(pw);
       }
-      // padding: the kernel reads each 4-byte pull word with its successor
-      pairs.push_back(PairRec{});
       lay.n_prec = int(plan.slot_i.size());
     } else {
       for (size_t p = 0; p < pi_new.size(); ++p) pairs.push_back(record(pi_new[p], pj_new[p]));

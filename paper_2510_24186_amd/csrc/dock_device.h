@@ -141,16 +141,19 @@ DK_INLINE float group_scan(float v) {
 }
 
 // ------------------------------------------------------------------ terms
-// Pair word: i | j << 8 | type_i << 16 | type_j << 20 | flags << 24, plus the
-// radius sum as a float.  flags bit0 donor/acceptor pair, bit1 both
-// hydrophobic, bit7 empty slot (no pair).
+// Pair word: i | j << 8 | l2 << 16 | flags << 24, plus the radius sum as a
+// float.  flags bit0 donor/acceptor pair, bit1 both hydrophobic, bit7 empty
+// slot (no pair); l2: byte offset of the pair's log2(d_clash) in the table
+// that is staged behind a pass layout's records (kClashTable floats).
 // Pass layout: each slot takes two entries, the pair word and radius sum,
-// then the E_clash constants d_clash^2 (negated for a donor/acceptor pair)
-// and log2(d_clash) (FP32 bit patterns in a second PairRec), so record p
-// still starts at entry 2p; after the n_prec slots come the pull bytes,
-// apl * cap per lane and pass (see PassPlan).  An empty slot names atoms 0
-// and 0 with a radius sum of -1e4 and zero clash constants, which makes every
-// term of both presets exactly zero.
+// then d_clash^2 (FP32 bits, negated for a donor/acceptor pair) and the first
+// four pull bytes of the slot's lane and pass (see PassPlan), so record p
+// still starts at entry 2p and one 16-byte read brings a lane all that a
+// pass needs; where a lane has eight pull bytes per pass (apl * cap), the
+// other four follow after the n_prec slots, one word per slot.  Then the
+// table of log2(d_clash), which only the energy reads.  An empty slot
+// names atoms 0 and 0 with a radius sum of -1e4 and a zero clash distance,
+// which makes every term of both presets exactly zero.
 constexpr uint32_t kPairEmpty = 0x80u << 24;
 constexpr float kEmptyRsum = -1.0e4f;
 struct PairRec {
@@ -184,10 +187,8 @@ DK_INLINE uint4 lds_read_u4(uint32_t a) {
   const u32x4_t v = *(const __attribute__((address_space(3))) u32x4_t*)(uintptr_t)a;
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-// two consecutive dwords at a 4-byte aligned address (one ds_read2_b32)
-DK_INLINE uint2 lds_read_u2(uint32_t a) {
-  const __attribute__((address_space(3))) uint32_t* p = (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)a;
-  return make_uint2(p[0], p[1]);
+DK_INLINE uint32_t lds_read_u1(uint32_t a) {
+  return *(const __attribute__((address_space(3))) uint32_t*)(uintptr_t)a;
 }
 DK_INLINE void lds_write4(uint32_t a, float x, float y, float z) {
   const f32x4_t v = {x, y, z, 0.f};
@@ -215,6 +216,13 @@ typedef int i32x2_t __attribute__((ext_vector_type(2)));
 DK_INLINE int2 ldg(const int2* p) {
   const i32x2_t v = *(const __attribute__((address_space(1))) i32x2_t*)p;
   return make_int2(v.x, v.y);
+}
+
+// a * b rounded to FP32, never fused into a following sum: pair distances
+// keep the same bits in every kernel and loop they are evaluated in.
+DK_INLINE float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
 }
 
 // exp(x) on the hardware exp2 (v_exp_f32): callers pass x * log2(e) already
@@ -256,9 +264,9 @@ DK_INLINE void trids_pair(float d2, float d, float rsum, uint32_t flags, const f
   }
 }
 
-// The TRIDS terms as trids_pair, with the clash cutoff and log2 of the clash
-// distance taken from the slot record (|dc2| = d_clash^2, negative for a
-// donor/acceptor pair; l2dc = log2 d_clash): -log(dd / dc) =
+// The TRIDS terms as trids_pair, with the clash cutoff taken from the slot
+// record and log2 of the clash distance from its table (|dc2| = d_clash^2,
+// negative for a donor/acceptor pair; l2dc = log2 d_clash): -log(dd / dc) =
 // -ln2 (log2 dd - log2 dc), and for d > 0.1 the derivative -1/d comes from
 // the caller's 1/d.
 DK_INLINE void trids_pair_k(float d2, float d, float inv_d, float rsum, float dc2, float l2dc,
@@ -274,10 +282,12 @@ DK_INLINE void trids_pair_k(float d2, float d, float inv_d, float rsum, float dc
     if (far) de -= w[1] * inv_d;
   }
   // few slots hold a donor/acceptor pair inside 3.4 A: the term is skipped
-  // unless some lane of the wave needs it
+  // unless some lane of the wave needs it (the empty asm keeps the compiler
+  // from evaluating it always and selecting)
   const bool hb_in = (dc2 < 0.f) & (d2 < 3.4f * 3.4f);
   if (__builtin_amdgcn_ballot_w64(hb_in)) {
-    const float t = d - 2.88f;
+    float t = d - 2.88f;
+    asm volatile("" : "+v"(t));
     const float eh = hb_in ? exp2_hw(t * t * (-kLog2e / 0.18f)) : 0.f;
     e -= w[2] * eh;
     de += (w[2] * (2.0f / 0.18f)) * t * eh;
@@ -960,19 +970,19 @@ DK_INLINE float pair_force(const LaneLig<APL>& L, const PairRec& pr, const float
 }
 
 // pair_force for a pass-layout slot: coordinates as read from the slab, the
-// clash constants from the slot's second entry.
-template <int APL>
-DK_INLINE float pair_force_slot(const LaneLig<APL>& L, const uint4& rp, const f32x4_t& xi, const f32x4_t& xj,
-                                float (&f)[3]) {
+// clash cutoff from the slot's second entry.
+template <int APL, bool TRIDS>
+DK_INLINE float pair_force_slot(const LaneLig<APL>& L, const uint4& rp, float l2dc, const f32x4_t& xi,
+                                const f32x4_t& xj, float (&f)[3]) {
   const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
   const float d2 = dx * dx + dy * dy + dz * dz;
   // d2 = 0 (coincident atoms) gives d = 0 and a finite 1/d
   const float inv_d = __builtin_amdgcn_rsqf(fmaxf(d2, 1e-30f));
-  const float d = d2 * inv_d;
+  const float d = mul_rounded(d2, inv_d);
   const float rsum = __uint_as_float(rp.y);
   float e, de;
-  if (L.preset == DOCK_PRESET_TRIDS)
-    trids_pair_k(d2, d, inv_d, rsum, __uint_as_float(rp.z), __uint_as_float(rp.w), L.w, e, de);
+  if (TRIDS)
+    trids_pair_k(d2, d, inv_d, rsum, __uint_as_float(rp.z), l2dc, L.w, e, de);
   else
     vina_pair(d2, d, rsum, rp.x >> 24, L.w, e, de);
   const float c = de * inv_d;
@@ -984,31 +994,24 @@ DK_INLINE float pair_force_slot(const LaneLig<APL>& L, const uint4& rp, const f3
 
 // Pass-layout gather: each atom of the lane reads CAP force entries, the
 // first CAP/2 added and the rest subtracted, all reads issued before the
-// first sum.  The lane's pull bytes (APL * CAP of them) are packed in pw:
-// CAP 8: x then y; CAP 4: atom s in word s; CAP 2: atom s in bytes 2s, 2s+1.
-// `between` runs after the reads are issued and before the sums (the next
-// pass's position reads go there, so their latency overlaps the sums).
-template <int APL, int CAP, class Between>
-DK_INLINE void gather_forces(const uint2& pw, uint32_t fb_a, float (&fsum)[APL][3], Between&& between) {
-  uint32_t ad[APL][CAP];
+// first sum.  The lane's pull bytes (APL * CAP of them) are packed in two
+// words: CAP 8: first then second; CAP 4: atom s in word s; CAP 2: atom s in
+// bytes 2s, 2s+1 of the first.
+template <int APL, int CAP>
+DK_INLINE void gather_addresses(uint32_t w0, uint32_t w1, uint32_t fb_a, uint32_t (&ad)[APL][CAP]) {
 #pragma unroll
   for (int s = 0; s < APL; ++s)
 #pragma unroll
     for (int c = 0; c < CAP; ++c) {
-      uint32_t word;
-      int k;
-      if (CAP == 8) {
-        word = c < 4 ? pw.x : pw.y;
-        k = c & 3;
-      } else if (CAP == 4) {
-        word = s == 0 ? pw.x : pw.y;
-        k = c;
-      } else {
-        word = pw.x;
-        k = 2 * s + c;
-      }
-      ad[s][c] = lds_entry16_k(word, k, fb_a);
+      const int k = CAP == 8 ? c & 3 : (CAP == 4 ? c : 2 * s + c);
+      const bool second = CAP == 8 ? c >= 4 : (CAP == 4 ? s == 1 : false);
+      ad[s][c] = lds_entry16_k(second ? w1 : w0, k, fb_a);
     }
+}
+// `between` runs after the reads are issued and before the sums (the next
+// pass's position reads go there, so their latency overlaps the sums).
+template <int APL, int CAP, class Between>
+DK_INLINE void gather_forces(const uint32_t (&ad)[APL][CAP], float (&fsum)[APL][3], Between&& between) {
   // all addresses first: no VALU-to-LDS-address wait states between reads
   __builtin_amdgcn_sched_barrier(0);
   f32x4_t v[APL][CAP];
@@ -1099,9 +1102,7 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
     const int W = L.pass_w;
     const bool slot_lane = r < W;
     // pull bytes: APL * cap per lane and pass (4 or 8), the lane's atoms one
-    // after the other.  Two consecutive dwords are always read (one
-    // ds_read2_b32); with 4 bytes the second belongs to the next lane (or the
-    // padding entry the host stages after the pull bytes) and is unused.
+    // after the other: four in the slot's record, the others behind them.
     const int cap = L.pull_cap;
     const uint32_t xs_a = lds_addr(S.xs), fb_a = lds_addr(S.fb);
     if (WG && r == 0) {
@@ -1113,17 +1114,21 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
     }
     // lanes without a slot hold no atom either: their gather is unused
     const uint32_t lane_slot = slot_lane ? uint32_t(r) : 0u;
-    const uint32_t recs_a = lds_addr(pairs), pulls_a = recs_a + 16u * uint32_t(L.n_prec);
-    // one loop per cap, so the gather's results stay in the same registers
-    // from pass to pass
-    auto run_passes = [&](auto cap_c) {
+    const uint32_t recs_a = lds_addr(pairs);
+    // one loop per cap and preset, so the gather's results stay in the same
+    // registers from pass to pass and a pass has no branch on either
+    auto run_passes = [&](auto cap_c, auto trids_c) {
       constexpr int CAP = decltype(cap_c)::value;
-      constexpr uint32_t kPullBytes = APL * CAP;
-      // this lane's record and pull word of the next pass are read before
-      // this pass's gather, and the record's two positions during it, so
-      // that their latency overlaps the gather and the sums
-      uint32_t rec_a = recs_a + 16u * lane_slot, pw_a = pulls_a + kPullBytes * lane_slot;
-      const uint32_t rec_step = 16u * uint32_t(W), pw_step = kPullBytes * uint32_t(W);
+      constexpr bool TRIDS = decltype(trids_c)::value, kTwoWords = APL * CAP == 8;
+      // this lane's record of the next pass is read before this pass's
+      // forces, and that record's two positions during the gather, so that
+      // their latency overlaps the forces, the gather and the sums
+      uint32_t rec_a = recs_a + 16u * lane_slot;
+      const uint32_t rec_step = 16u * uint32_t(W);
+      const uint32_t l2_a = recs_a + (APL * cap == 8 ? 20u : 16u) * uint32_t(L.n_prec);
+      auto l2_of = [&](const uint4& rec) {
+        return WE && TRIDS ? __uint_as_float(lds_read_u1(__builtin_amdgcn_udot4(rec.x, 1u << 16, l2_a, false))) : 0.f;
+      };
       uint4 rp = lds_read_u4(rec_a);
       if (!WG) {
         // the energy alone: nothing is exchanged between the passes, so the
@@ -1131,64 +1136,77 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
         // latency is waited for
         f32x4_t xi = lds_read4(lds_entry16<0>(rp.x, xs_a));
         f32x4_t xj = lds_read4(lds_entry16<1>(rp.x, xs_a));
+        float l2 = l2_of(rp);
         if (L.n_pass > 1) rec_a += rec_step;
         uint4 rp1 = lds_read_u4(rec_a);
         for (int ps = 0; ps < L.n_pass; ++ps) {
           if (ps + 2 < L.n_pass) rec_a += rec_step;
           const f32x4_t yi = lds_read4(lds_entry16<0>(rp1.x, xs_a)), yj = lds_read4(lds_entry16<1>(rp1.x, xs_a));
+          const float m2 = l2_of(rp1);
           const uint4 rp2 = lds_read_u4(rec_a);
           float f[3];
-          const float e = pair_force_slot(L, rp, xi, xj, f);
+          const float e = pair_force_slot<APL, TRIDS>(L, rp, l2, xi, xj, f);
           if (slot_lane) e_lane += e;
           rp = rp1;
           rp1 = rp2;
           xi = yi;
           xj = yj;
+          l2 = m2;
         }
         return;
       }
-      uint2 pw = lds_read_u2(pw_a);
+      uint32_t pw_a = recs_a + 16u * uint32_t(L.n_prec) + 4u * lane_slot;
+      const uint32_t pw_step = 4u * uint32_t(W);
+      uint32_t w1 = kTwoWords ? lds_read_u1(pw_a) : 0u;
+      float l2 = l2_of(rp);
       f32x4_t xi = lds_read4(lds_entry16<0>(rp.x, xs_a));
       f32x4_t xj = lds_read4(lds_entry16<1>(rp.x, xs_a));
-      for (int ps = 0; ps < L.n_pass; ++ps) {
+      auto one_pass = [&](bool more) {
         // the unused 4th components stay live until here: otherwise their
         // registers are reused for the gather's sums, which must then wait
         // for these reads to land
         asm volatile("" ::"v"(xi.w), "v"(xj.w));
+        uint32_t ad[APL][CAP];
+        gather_addresses<APL, CAP>(rp.w, w1, fb_a, ad);
+        if (more) {
+          rec_a += rec_step;
+          pw_a += pw_step;
+        }
+        const uint4 nxt = lds_read_u4(rec_a);
+        if (kTwoWords) w1 = lds_read_u1(pw_a);
         float f[3];
-        const float e = pair_force_slot(L, rp, xi, xj, f);
+        const float e = pair_force_slot<APL, TRIDS>(L, rp, l2, xi, xj, f);
         if (slot_lane) {
           if (WE) e_lane += e;
           lds_write4(fb_a + 16u * uint32_t(r), f[0], f[1], f[2]);
         }
-        if (ps + 1 < L.n_pass) {
-          rec_a += rec_step;
-          pw_a += pw_step;
-        }
-        const uint4 rp_next = lds_read_u4(rec_a);
-        const uint2 pw_next = lds_read_u2(pw_a);
         wave_sync();
         // every entry of the lane is read before any is summed
-        gather_forces<APL, CAP>(pw, fb_a, fsum, [&] {
-          const uint32_t ai = lds_entry16<0>(rp_next.x, xs_a), aj = lds_entry16<1>(rp_next.x, xs_a);
+        gather_forces<APL, CAP>(ad, fsum, [&] {
+          const uint32_t ai = lds_entry16<0>(nxt.x, xs_a), aj = lds_entry16<1>(nxt.x, xs_a);
           xi = lds_read4(ai);
           xj = lds_read4(aj);
+          l2 = l2_of(nxt);
         });
-        rp = rp_next;
-        pw = pw_next;
+        rp = nxt;
         wave_sync();
-      }
+      };
+      for (int ps = L.n_pass; ps; --ps) one_pass(ps > 1);
     };
     // caps: 4 or 8 with one atom per lane, 2 or 4 with two (the energy alone
     // gathers nothing: any cap's loop)
-    if (!WG)
-      run_passes(std::integral_constant<int, 4>{});
-    else if (APL == 2 && cap == 2)
-      run_passes(std::integral_constant<int, 2>{});
-    else if (APL == 2 || cap == 4)
-      run_passes(std::integral_constant<int, 4>{});
+    auto run_preset = [&](auto trids_c) {
+      if (!WG || (APL == 1 && cap == 4))
+        run_passes(std::integral_constant<int, 4>{}, trids_c);
+      else if (APL == 2 && cap == 2)
+        run_passes(std::integral_constant<int, 2>{}, trids_c);
+      else
+        run_passes(std::integral_constant<int, APL == 2 ? 4 : 8>{}, trids_c);
+    };
+    if (L.preset == DOCK_PRESET_TRIDS)
+      run_preset(std::true_type{});
     else
-      run_passes(std::integral_constant<int, 8>{});
+      run_preset(std::false_type{});
   } else {
     // ---- strided: lane r takes records r, r + LPP, ...; forces by LDS atomics
     if (WG) {

@@ -184,6 +184,9 @@ constexpr int kMaxPull = 8;
 // within 64 KiB of LDS.  The largest layouts of 65-70-atom ligands with
 // ~2,100 pairs stage ~41 KiB.
 constexpr size_t kPassStageBytes = 43 * 1024;
+// log2(d_clash) of the type pairs' distinct clash distances (six), staged
+// with every pass layout.
+constexpr int kClashTable = 8;
 struct PassPlan {
   int n_pass = 0, cap = 0, n_pull = 0;
   std::vector<int> slot_i, slot_j;
