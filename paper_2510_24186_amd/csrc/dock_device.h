@@ -422,6 +422,9 @@ DK_INLINE void pair_terms_unweighted(int preset, float d2, double d, double rsum
 // ------------------------------------------------------------------ trilinear
 // Cell = floor((p - o) / h) clamped to [0, n-2] at the clamped point; value,
 // analytic cell-local gradient, and the out-of-box penalty 10 |p - clamp(p)|_1.
+// a * b for operands below 2^24 with a product below 2^32 (v_mul_u32_u24)
+DK_INLINE uint32_t mul_u24(uint32_t a, uint32_t b) { return (a & 0xffffffu) * (b & 0xffffffu); }
+
 struct Trilerp {
   float v, gx, gy, gz, eout;
   int base;          // flat index of corner (0,0,0)
@@ -443,7 +446,8 @@ DK_INLINE void cell_axis(float p, float o, float hi, float inv_h, int n, float& 
   f = FUSED ? __builtin_fmaf(pc - o, inv_h, -float(c)) : u - float(c);
 }
 
-DK_INLINE Trilerp trilerp(const float* __restrict__ M, const GridDev& g, float px, float py, float pz) {
+// M: the maps of one pocket, `first` the float index of the wanted map.
+DK_INLINE Trilerp trilerp(const float* __restrict__ M, uint64_t first, const GridDev& g, float px, float py, float pz) {
   Trilerp t;
   float pcx, pcy, pcz;
   bool ix, iy, iz;
@@ -451,10 +455,11 @@ DK_INLINE Trilerp trilerp(const float* __restrict__ M, const GridDev& g, float p
   cell_axis<false>(px, g.origin[0], g.hi[0], g.inv_spacing, g.dims[0], pcx, ix, cx, t.fx);
   cell_axis<true>(py, g.origin[1], g.hi[1], g.inv_spacing, g.dims[1], pcy, iy, cy, t.fy);
   cell_axis<true>(pz, g.origin[2], g.hi[2], g.inv_spacing, g.dims[2], pcz, iz, cz, t.fz);
-  // nodes per map <= 2^30: 32-bit node indices
+  // dims <= 1024: rows and nodes from full-rate 24-bit products (a 32-bit
+  // integer product takes four times as long), node indices below 2^30
   const uint32_t nx = uint32_t(g.dims[0]), nxy = uint32_t(g.dims[0]) * uint32_t(g.dims[1]);
-  t.base = int((uint32_t(cz) * uint32_t(g.dims[1]) + uint32_t(cy)) * nx + uint32_t(cx));
-  const float* p0 = M + uint32_t(t.base);
+  t.base = int(mul_u24(mul_u24(uint32_t(cz), uint32_t(g.dims[1])) + uint32_t(cy), nx) + uint32_t(cx));
+  const float* p0 = M + (first + uint32_t(t.base));
   const float c000 = ldg(p0), c100 = ldg(p0 + 1), c010 = ldg(p0 + nx), c110 = ldg(p0 + nx + 1);
   const float c001 = ldg(p0 + nxy), c101 = ldg(p0 + nxy + 1), c011 = ldg(p0 + nxy + nx),
               c111 = ldg(p0 + nxy + nx + 1);
@@ -886,34 +891,41 @@ DK_INLINE float chain_rule(const LaneLig<APL>& L, const Rigid& rg, const float (
   // inclusive scan over lanes (lane r covers atoms up to APL*r + APL - 1)
 #pragma unroll
   for (int k = 0; k < 6; ++k) v[k] = group_scan<LPP>(v[k]);
-  // prefix at an atom boundary: P(end) = sum of atoms [0, end)
-  // lane holding atoms [APL*l, APL*l+APL): inclusive value v; with APL = 2,
-  // the partial up to its first atom is v - vs[1].
-  float vlast[6];
-  float vfirst[6];
+  // prefix at an atom boundary: P(end) = sum of atoms [0, end).  Every lane
+  // leaves the inclusive values of its atoms in the slab (the force entries
+  // are free by now): with APL = 2 the partial up to its first atom is
+  // v - vs[1].  Two reads per boundary take the place of 6 * APL cross-lane
+  // fetches.
+  constexpr int NA = LPP * APL;
+  const uint32_t pa = lds_addr(S.fb), pc = pa + 16u * NA;
+  wave_sync();
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    vlast[k] = v[k];
-    vfirst[k] = APL == 2 ? v[k] - vs[APL - 1][k] : v[k];
+  for (int s = 0; s < APL; ++s) {
+    float u[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) u[k] = (APL == 2 && s == 0) ? v[k] - vs[APL - 1][k] : v[k];
+    const uint32_t a = uint32_t(APL * r + s);
+    *(__attribute__((address_space(3))) f32x4_t*)(uintptr_t)(pa + 16u * a) = f32x4_t{u[0], u[1], u[2], u[3]};
+    *(__attribute__((address_space(3))) f32x2_t*)(uintptr_t)(pc + 8u * a) = f32x2_t{u[4], u[5]};
   }
+  wave_sync();
   auto prefix = [&](int end, float* out) {
     // all lanes call this with their own `end`; returns sum over [0, end)
-    const int a = end - 1;
-    const int ad = bp_addr<LPP>(a >= 0 ? a / APL : 0);
-    const bool first = APL == 2 && (a % APL) == 0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const float lv = bp(ad, vlast[k]);
-      const float fv = APL == 2 ? bp(ad, vfirst[k]) : lv;
-      out[k] = a < 0 ? 0.f : (first ? fv : lv);
-    }
+    const uint32_t a = uint32_t(max(end - 1, 0));
+    const f32x4_t p = *(const __attribute__((address_space(3))) f32x4_t*)(uintptr_t)(pa + 16u * a);
+    const f32x2_t q = *(const __attribute__((address_space(3))) f32x2_t*)(uintptr_t)(pc + 8u * a);
+    out[0] = p.x; out[1] = p.y; out[2] = p.z; out[3] = p.w;
+    out[4] = q.x; out[5] = q.y;
   };
   // rigid lanes need the total (prefix at n_atoms minus prefix at 0), torsion
   // lanes their subtree's range: one pair of prefix lookups serves both
   const bool rigid = r < 6;
   float pb[6], pe[6];
-  prefix(rigid ? 0 : L.tsb, pb);
+  const int begin = rigid ? 0 : L.tsb;
+  prefix(begin, pb);
   prefix(rigid ? L.n_atoms : L.tse, pe);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) pb[k] = begin > 0 ? pb[k] : 0.f;
   float Sg[3], St[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -1053,12 +1065,11 @@ constexpr int kModeGrid = 0, kModeDirect = 1, kModeGridMdn = 2;
 constexpr int kWantE = 1, kWantG = 2, kWantBoth = 3;
 
 template <int LPP, int APL, int WANT = kWantBoth, bool WANT_X = false, int MODE = kModeGrid>
-DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& pk,
+DK_INLINE EvalOut eval_pose(LaneLig<APL>& L, float q, const PocketDev& pk,
                             const PairRec* __restrict__ pairs, const GroupSlab& S, int r,
                             float (*xo)[3] = nullptr, float (*go)[3] = nullptr,
                             const MdnArg& mdn = MdnArg{nullptr, 0, 0}) {
   constexpr bool WE = (WANT & kWantE) != 0, WG = (WANT & kWantG) != 0;
-  LaneLig<APL> L = Lin;
   launder(L);
   // ---- atoms: place, interpolate, publish coordinates to the slab
   float x[APL][3], g[APL][3];
@@ -1074,8 +1085,9 @@ DK_INLINE EvalOut eval_pose(const LaneLig<APL>& Lin, float q, const PocketDev& p
                      g[s][2]);
         e_lane += ei;
       } else {
-        const size_t nxyz = size_t(pk.grid.dims[0]) * pk.grid.dims[1] * pk.grid.dims[2];
-        const Trilerp tl = trilerp(pk.M + size_t(L.atype[s]) * nxyz, pk.grid, x[s][0], x[s][1], x[s][2]);
+        const uint32_t nxyz = uint32_t(pk.grid.dims[0]) * uint32_t(pk.grid.dims[1]) * uint32_t(pk.grid.dims[2]);
+        const Trilerp tl =
+            trilerp(pk.M, uint64_t(uint32_t(L.atype[s])) * nxyz, pk.grid, x[s][0], x[s][1], x[s][2]);
         e_lane += tl.v + tl.eout;
         g[s][0] = tl.gx;
         g[s][1] = tl.gy;
@@ -1306,7 +1318,7 @@ DK_INLINE float eval_terms(const LaneLig<APL>& L, float q, float (&x)[APL][3], f
       const float* base = G + size_t(L.atype[s]) * K * nxyz;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const Trilerp tl = trilerp(base + size_t(k) * nxyz, grid, x[s][0], x[s][1], x[s][2]);
+        const Trilerp tl = trilerp(base + size_t(k) * nxyz, 0, grid, x[s][0], x[s][1], x[s][2]);
         el[k] += tl.v;
         if (k == 0) eout += tl.eout;  // the out-of-box penalty is the same for every term
         // trilerp() adds the out-of-box slope to its gradient; remove it from

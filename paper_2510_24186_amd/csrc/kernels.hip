@@ -566,7 +566,7 @@ DK_INLINE float wrap_clamp(float q, int r, const LaneLig<APL>& L) {
 // from 46.8 to 43.0 ms, 2,048 ligands of 10-70 atoms in 16 pockets x 64 x 30
 // from 83.2 to 65.1 ms (the kernel is bound by VALU issue, then LDS).
 template <int LPP, int APL, int MODE, bool FULL>
-DK_INLINE void run_traj(const SampleArgs& a, const LaneLig<APL>& L, const PocketDev& pk, const MdnArg& mdn,
+DK_INLINE void run_traj(const SampleArgs& a, LaneLig<APL>& L, const PocketDev& pk, const MdnArg& mdn,
                         const PairRec* pairs,
                         const GroupSlab& S, int lig, int traj, int r) {
   const size_t ti = size_t(lig) * a.n_traj + traj;
