@@ -2137,7 +2137,18 @@ int dock_pocket_map_adjoint(dock_pocket_t p, const float* dLdG, float* dLdxyz, d
   a.lam = dLdG;
   a.dLdxyz = dLdxyz;
   a.dLdtheta = dLdtheta;
-  HIP_TRY(launch_map_adjoint(a, reinterpret_cast<hipStream_t>(stream)));
+  // brick flags in stream-ordered scratch; a call under capture (which would
+  // record the allocation) or without memory for it does without
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (p->n_rec > 0 && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+      hipMallocAsync(reinterpret_cast<void**>(&a.flag), size_t(map_adjoint_bricks(a.grid)), s) != hipSuccess) {
+    (void)hipGetLastError();
+    a.flag = nullptr;
+  }
+  const hipError_t e = launch_map_adjoint(a, s);
+  if (a.flag) (void)hipFreeAsync(a.flag, s);
+  HIP_TRY(e);
   return DOCK_OK;
 } catch (...) {
   return exception_status();

@@ -390,35 +390,6 @@ DK_INLINE void pair_terms_f32(float d2, float d, float rsum, uint32_t flags, flo
   }
 }
 
-// Per-term values (no weights) of a receptor/ligand type pair for the map
-// build: each term's inside-cutoff decision is taken on the FP32 squared
-// distance d2; the values are evaluated in FP64 from the FP64 distance d.
-DK_INLINE void pair_terms_unweighted(int preset, float d2, double d, double rsum, float dclash2,
-                                     double dclash, uint32_t flags, double* v) {
-  if (preset == DOCK_PRESET_TRIDS) {
-    v[0] = v[1] = v[2] = 0.0;
-    if (d2 < 100.0f) {
-      const double s = d - rsum - 3.0;
-      v[0] = -exp(-0.25 * s * s);
-    }
-    if (d2 < dclash2) v[1] = -log(fmax(d, 0.1) / dclash);
-    if ((flags & 1u) && d2 < 3.4f * 3.4f) {
-      const double t = d - 2.88;
-      v[2] = -exp(-t * t / 0.18);
-    }
-  } else {
-    v[0] = v[1] = v[2] = v[3] = v[4] = 0.0;
-    if (!(d2 < 64.0f)) return;
-    const double s = d - rsum;
-    v[0] = exp(-4.0 * s * s);
-    const double t = s - 3.0;
-    v[1] = exp(-0.25 * t * t);
-    v[2] = s < 0.0 ? s * s : 0.0;
-    if (flags & 2u) v[3] = s < 0.5 ? 1.0 : (s < 1.5 ? 1.5 - s : 0.0);
-    if (flags & 1u) v[4] = s < -0.7 ? 1.0 : (s < 0.0 ? -s / 0.7 : 0.0);
-  }
-}
-
 // ------------------------------------------------------------------ trilinear
 // Cell = floor((p - o) / h) clamped to [0, n-2] at the clamped point; value,
 // analytic cell-local gradient, and the out-of-box penalty 10 |p - clamp(p)|_1.

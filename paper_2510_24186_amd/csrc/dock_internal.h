@@ -84,6 +84,32 @@ struct alignas(16) TypePair {
   double dclash64;
 };
 
+// Type radii (Angstrom) and flags; order C_H C_P N_P N_D N_A O_A O_DA Cl_H.
+constexpr double kRadius[kTypes] = {1.9, 1.9, 1.8, 1.8, 1.8, 1.7, 1.7, 1.8};
+constexpr bool kHydrophobic[kTypes] = {true, false, false, false, false, false, false, true};
+constexpr bool kDonor[kTypes] = {false, false, false, true, false, false, true, false};
+constexpr bool kAcceptor[kTypes] = {false, false, false, false, true, true, true, false};
+
+// Classes of ligand types with equal terms against every receptor type: by
+// radius, and by radius and donor / acceptor role (the clash term; a class
+// that is neither has no hydrogen-bond term).  kRadType / kRoleType: a type of
+// each class; kRoleRad: the role class's radius class.
+constexpr int kRadClasses = 3, kRoleClasses = 6;
+constexpr int kRadClass[kTypes] = {0, 0, 1, 1, 1, 2, 2, 1};
+constexpr int kRadType[kRadClasses] = {0, 2, 5};
+constexpr int kRoleClass[kTypes] = {0, 0, 1, 2, 3, 4, 5, 1};
+constexpr int kRoleType[kRoleClasses] = {0, 2, 3, 4, 5, 6};
+constexpr int kRoleRad[kRoleClasses] = {0, 1, 1, 1, 2, 2};
+constexpr bool classes_hold() {
+  for (int t = 0; t < kTypes; ++t) {
+    const int r = kRadType[kRadClass[t]], c = kRoleType[kRoleClass[t]];
+    if (kRadius[t] != kRadius[r] || kRadius[t] != kRadius[c] || kRadClass[t] != kRoleRad[kRoleClass[t]]) return false;
+    if (kDonor[t] != kDonor[c] || kAcceptor[t] != kAcceptor[c]) return false;
+  }
+  return true;
+}
+static_assert(classes_hold(), "type classes");
+
 // Grid geometry of one pocket.
 struct GridDev {
   float origin[3];

@@ -151,7 +151,10 @@ struct MapAdjArgs {
   const float* lam;    // dL/dG [8][3][nodes]
   float* dLdxyz;       // [n_rec * 3], +=
   double* dLdtheta;    // [kMapTheta], +=
+  unsigned char* flag; // scratch, one byte per brick of nodes (map_adjoint_bricks), or null:
+                       // every brick counts as holding a nonzero lambda
 };
+long long map_adjoint_bricks(const GridDev& g);
 hipError_t launch_map_adjoint(const MapAdjArgs& a, hipStream_t s);
 
 // LDS bytes a sampler block of `block` threads needs.

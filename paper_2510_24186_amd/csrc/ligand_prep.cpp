@@ -17,12 +17,6 @@ namespace dock {
 
 namespace {
 
-// Type radii (Angstrom) and flags; order C_H C_P N_P N_D N_A O_A O_DA Cl_H.
-const double kRadius[kTypes] = {1.9, 1.9, 1.8, 1.8, 1.8, 1.7, 1.7, 1.8};
-const bool kHydrophobic[kTypes] = {true, false, false, false, false, false, false, true};
-const bool kDonor[kTypes] = {false, false, false, true, false, false, true, false};
-const bool kAcceptor[kTypes] = {false, false, false, false, true, true, true, false};
-
 enum { T_C_H, T_C_P, T_N_P, T_N_D, T_N_A, T_O_A, T_O_DA, T_CL_H };
 
 std::vector<int> bfs_levels(const std::vector<std::vector<int>>& adj, int src) {
