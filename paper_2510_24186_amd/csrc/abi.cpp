@@ -1036,9 +1036,7 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
   a.dEdq = dEdq;
   a.xyz = xyz_out;
   a.xyz_stride = xyz_stride;
-  a.max_pairs = L->max_alt_pairs;
-  HIP_TRY(launch_score(a, lpp, apl, eval_mode(pockets, n_pockets, L),
-                       reinterpret_cast<hipStream_t>(stream)));
+  HIP_TRY(launch_score(a, apl == 2, eval_mode(pockets, n_pockets, L), reinterpret_cast<hipStream_t>(stream)));
   return DOCK_OK;
 } catch (...) {
   return exception_status();

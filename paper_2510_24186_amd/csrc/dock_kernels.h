@@ -31,7 +31,8 @@ struct ScoreArgs {
   float* dEdq;
   float* xyz;
   int xyz_stride;
-  int max_pairs;
+  int chunk;            // poses per wavefront
+  unsigned slab_bytes;  // LDS of a wavefront's slabs
 };
 
 constexpr int kMaxDiffPockets = 16;
@@ -163,7 +164,8 @@ size_t score_lds_bytes(int lpp, int apl, int max_pairs);
 
 hipError_t launch_map_build(const MapArgs& a, hipStream_t s);
 // mode: 0 grid maps, 1 direct pair sums, 2 grid maps + E_MDN
-hipError_t launch_score(const ScoreArgs& a, int lpp, int apl, int mode, hipStream_t s);
+// (two_per_lane: some ligand of the handle has more than 64 atoms)
+hipError_t launch_score(ScoreArgs a, bool two_per_lane, int mode, hipStream_t s);
 hipError_t launch_sample(const SampleArgs& a, int lpp, int apl, int grid, int block, int mode,
                          hipStream_t s);
 hipError_t launch_best(const BestArgs& a, hipStream_t s);

@@ -447,6 +447,7 @@ DK_INLINE GroupSlab make_slab(unsigned char* base) {
   S.fy = S.fx + NA;
   S.fz = S.fy + NA;
   S.fb = reinterpret_cast<float4*>(S.fx);
+  S.l2 = nullptr;
   return S;
 }
 // coordinates (16 B per atom), then the larger of three FP64 force arrays
@@ -483,33 +484,75 @@ DK_INLINE MdnArg mdn_for(const LigandArrays& A, const LigDev& lg, const PocketDe
 
 // ================================================================ score
 
+// A wavefront takes `chunk` consecutive poses and evaluates as many at a time
+// as their ligands' lane configurations allow: four in 16-lane groups, two in
+// 32-lane groups, else one (one atom per lane up to 64 atoms).  Pair records
+// are read from global memory: a wave's LDS is its slabs alone, so the
+// registers and not the LDS set how many waves a CU holds (three per SIMD:
+// four spill 42 registers and ran 130 us where three take 109).  32,768 poses
+// of 256 ligands of 10-60 atoms: 370 us with records staged per group and
+// every pose in the lane configuration of the largest ligand, 109 us so.
+struct WaveForm {
+  int lanes, poses;  // lanes per pose (16, 32, 64; 128: 64 lanes, two atoms each), poses taken
+};
+// form of the poses from `at` on; cfg: per lane, the lane configuration of
+// pose `lane` of the chunk (16, 32, 64, 128; 0 past the chunk's end)
+DK_INLINE WaveForm next_form(int cfg, int at, int chunk) {
+  const int c = __builtin_amdgcn_readlane(cfg, at);
+  if (c > 32) return WaveForm{c, 1};
+  const unsigned long long le32 = __builtin_amdgcn_ballot_w64(cfg <= 32), le16 = __builtin_amdgcn_ballot_w64(cfg <= 16);
+  if (chunk - at >= 4 && ((le16 >> at) & 15u) == 15u) return WaveForm{16, 4};
+  if (chunk - at >= 2 && ((le32 >> at) & 3u) == 3u) return WaveForm{32, 2};
+  return WaveForm{64, 1};
+}
+// lane configuration of a ligand with one atom per lane up to 64 atoms
+DK_INLINE int lane_config(const LigDev* g) {
+  if (g->n_atoms > 64) return 128;
+  const int need = max(g->n_atoms, max(g->n_dof, g->n_frags));
+  return need <= 16 ? 16 : (need <= 32 ? 32 : 64);
+}
+// slabs of the forms: 4 of 16 lanes, 2 of 32, 1 of 64
+constexpr size_t wave_slab_bytes(bool two_per_lane) {
+  return two_per_lane ? slab_bytes(64, 2)
+                      : std::max({4 * slab_bytes(16, 1), 2 * slab_bytes(32, 1), slab_bytes(64, 1)});
+}
+constexpr size_t kClashBytes = sizeof(float) * kClashTable;
+size_t wave_lds_bytes(bool two_per_lane) { return wave_slab_bytes(two_per_lane) + 4 * kClashBytes; }
+
+// The log2(d_clash) table of a pass layout into the group's LDS.
+template <int LPP>
+DK_INLINE void stage_clash_table(const LigDev& lg, const PairRec* pairs, float* l2, int r) {
+  if (lg.n_pass > 0 && r < kClashTable) {
+    const size_t at = 2 * size_t(lg.n_prec) + (lg.pass_apl * lg.pull_cap == 8 ? size_t(lg.n_prec) / 2 : 0);
+    l2[r] = ldg(reinterpret_cast<const float*>(pairs + at) + r);
+  }
+}
+
 template <int LPP, int APL, int MODE>
-__global__ void __launch_bounds__(64) score_kernel(ScoreArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int GPB = 64 / LPP;
+DK_INLINE void score_poses(const ScoreArgs& a, long long first, unsigned char* smem, unsigned char* tables) {
   const int grp = threadIdx.x / LPP, r = threadIdx.x % LPP;
-  const long long pose = (long long)blockIdx.x * GPB + grp;
-  unsigned char* mine = smem + size_t(grp) * (pair_bytes(a.max_pairs) + slab_bytes(LPP, APL));
-  PairRec* gp = reinterpret_cast<PairRec*>(mine);
-  const GroupSlab S = make_slab<LPP, APL>(mine + pair_bytes(a.max_pairs));
+  const long long pose = first + grp;
   if (pose >= a.n_poses) return;
   const int lig = a.pose_lig[pose];
   if (lig < 0 || lig >= a.n_ligands) {
     if (r == 0) a.E[pose] = __int_as_float(0x7fc00000);
     return;
   }
-  // single-launch kernels use the alternative (one atom per lane up to 64
-  // atoms) pair layouts
+  GroupSlab S = make_slab<LPP, APL>(smem + size_t(grp) * slab_bytes(LPP, APL));
+  S.l2 = reinterpret_cast<float*>(tables + grp * kClashBytes);
+  // the alternative (one atom per lane up to 64 atoms) pair layouts
   LigDev lg = a.L.ligs[lig];
   use_alt_layout(lg);
   const PocketDev pk = a.pockets[lg.pocket];
   LaneLig<APL> L;
   load_lane_lig<LPP, APL>(L, lg, a.L.ligs + lig, a.L.atoms, a.L.frags, a.L.tors, pk, r);
-  for (int p = r; p < lg.n_stage; p += LPP) gp[p] = a.L.pairs[lg.pair_off + p];
+  const PairRec* pairs = a.L.pairs + lg.pair_off;
+  stage_clash_table<LPP>(lg, pairs, S.l2, r);
   wave_sync();
   const float q = r < lg.n_dof ? a.q[pose * a.q_stride + r] : 0.f;
   float xo[APL][3], go[APL][3];
-  const EvalOut o = eval_pose<LPP, APL, kWantBoth, true, MODE>(L, q, pk, gp, S, r, xo, go, mdn_for(a.L, lg, pk));
+  const EvalOut o =
+      eval_pose<LPP, APL, kWantBoth, true, MODE, true>(L, q, pk, pairs, S, r, xo, go, mdn_for(a.L, lg, pk));
   if (r == 0) a.E[pose] = o.E;
   if (a.dEdq && r < lg.n_dof) a.dEdq[pose * a.q_stride + r] = o.g;
   if (a.xyz) {
@@ -527,27 +570,49 @@ __global__ void __launch_bounds__(64) score_kernel(ScoreArgs a) {
 }
 
 template <int MODE>
-static hipError_t launch_score_t(const ScoreArgs& a, int lpp, int apl, unsigned blocks, size_t lds,
-                                 hipStream_t s) {
-  if (lpp == 16 && apl == 1)
-    hipLaunchKernelGGL((score_kernel<16, 1, MODE>), dim3(blocks), dim3(64), lds, s, a);
-  else if (lpp == 32 && apl == 1)
-    hipLaunchKernelGGL((score_kernel<32, 1, MODE>), dim3(blocks), dim3(64), lds, s, a);
-  else if (lpp == 64 && apl == 1)
-    hipLaunchKernelGGL((score_kernel<64, 1, MODE>), dim3(blocks), dim3(64), lds, s, a);
-  else
-    hipLaunchKernelGGL((score_kernel<64, 2, MODE>), dim3(blocks), dim3(64), lds, s, a);
-  return hipGetLastError();
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) score_kernel(ScoreArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* tables = smem + a.slab_bytes;
+  const long long base = (long long)blockIdx.x * a.chunk;
+  const int n = int(min((long long)a.chunk, a.n_poses - base));
+  int cfg = 0;
+  if (int(threadIdx.x) < n) {
+    const int lig = a.pose_lig[base + threadIdx.x];
+    if (lig >= 0 && lig < a.n_ligands) cfg = lane_config(a.L.ligs + lig);
+  }
+  for (int at = 0; at < n;) {
+    const WaveForm f = next_form(cfg, at, n);
+    if (f.lanes == 16)
+      score_poses<16, 1, MODE>(a, base + at, smem, tables);
+    else if (f.lanes == 32)
+      score_poses<32, 1, MODE>(a, base + at, smem, tables);
+    else if (f.lanes == 64)
+      score_poses<64, 1, MODE>(a, base + at, smem, tables);
+    else
+      score_poses<64, 2, MODE>(a, base + at, smem, tables);
+    wave_sync();
+    at += f.poses;
+  }
 }
 
-hipError_t launch_score(const ScoreArgs& a, int lpp, int apl, int mode, hipStream_t s) {
-  const int gpb = 64 / lpp;
-  const unsigned blocks = unsigned((a.n_poses + gpb - 1) / gpb);
-  const size_t lds = score_lds_bytes(lpp, apl, a.max_pairs);
-  if (blocks == 0) return hipSuccess;
-  if (mode == kModeDirect) return launch_score_t<kModeDirect>(a, lpp, apl, blocks, lds, s);
-  if (mode == kModeGridMdn) return launch_score_t<kModeGridMdn>(a, lpp, apl, blocks, lds, s);
-  return launch_score_t<kModeGrid>(a, lpp, apl, blocks, lds, s);
+// Poses per wavefront: one until the waves of one pose each would fill the
+// chip's wave slots (4 waves on each of the 1,024 SIMDs), then two, then four
+// (small ligands then share a wave).
+int wave_chunk(long long n_poses) { return n_poses <= 4096 ? 1 : (n_poses <= 8192 ? 2 : 4); }
+
+hipError_t launch_score(ScoreArgs a, bool two_per_lane, int mode, hipStream_t s) {
+  if (a.n_poses <= 0) return hipSuccess;
+  a.chunk = wave_chunk(a.n_poses);
+  a.slab_bytes = unsigned(wave_slab_bytes(two_per_lane));
+  const unsigned blocks = unsigned((a.n_poses + a.chunk - 1) / a.chunk);
+  const size_t lds = wave_lds_bytes(two_per_lane);
+  if (mode == kModeDirect)
+    hipLaunchKernelGGL(score_kernel<kModeDirect>, dim3(blocks), dim3(64), lds, s, a);
+  else if (mode == kModeGridMdn)
+    hipLaunchKernelGGL(score_kernel<kModeGridMdn>, dim3(blocks), dim3(64), lds, s, a);
+  else
+    hipLaunchKernelGGL(score_kernel<kModeGrid>, dim3(blocks), dim3(64), lds, s, a);
+  return hipGetLastError();
 }
 
 // ================================================================ differentiable form
