@@ -236,20 +236,23 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
  *   dLdG   host array [n_pockets] of device pointers (entries nullable) or NULL
  *   dLdw   device [n_pockets * K] or NULL;  dLdq, dLdx device or NULL
  * All pockets of a call share one preset; n_pockets <= 16.
- *   deterministic  0: dL/dG and dL/dw by float atomics (summation order, and
- *                     so the last bits, vary from call to call);
+ *   deterministic  0: dL/dG by float atomics (summation order, and so the last
+ *                     bits, vary from call to call; so does dL/dw in calls of
+ *                     fewer than 256 poses);
  *                  1: bitwise repeatable.  dL/dG is summed as 64-bit
  *                     integers: every corner contribution is rounded once to
  *                     a multiple of 2^(e - 62), where 2^e bounds any node's
  *                     sum (n_poses x max_p |dLdE_p| N_p x max_k |w_k|, per
  *                     pocket), so the sum is exact and order-free; then it is
  *                     converted and added to dLdG.  dL/dw is reduced over the
- *                     poses in a fixed order.  Scratch (8 bytes per dL/dG
- *                     entry, 4 (K + 1) bytes per pose) is allocated and
- *                     released on the stream.  Non-finite dLdE or w make
+ *                     poses in a fixed order.  Non-finite dLdE or w make
  *                     that pocket's dL/dG NaN.
- * Ligand-internal pair forces are summed as fixed point in either mode, so
- * E, dL/dq and dL/dx never depend on timing.
+ *   Scratch is allocated and released on the stream: 8 bytes per dL/dG entry
+ *   (deterministic) or 4 bytes per node and type (otherwise, from 256 poses
+ *   on and outside stream capture), of which only the surroundings of the
+ *   poses' atoms are touched, and 4 (K + 1) bytes per pose.
+ * Ligand-internal pair forces are summed in FP64 in a fixed order, or as
+ * fixed point, in either mode, so E, dL/dq and dL/dx never depend on timing.
  * ---------------------------------------------------------------------- */
 int dock_score_terms(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligands_t L,
                      int64_t n_poses, const int32_t* pose_lig, const float* q, int32_t q_stride,

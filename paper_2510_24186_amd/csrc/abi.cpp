@@ -195,10 +195,12 @@ static LaneCfg lane_cfg(const LigDev& lg, int force_lpp, bool one_per_lane = fal
   return c;
 }
 
-// One lane configuration wide enough for every ligand of a handle (the score
-// and differentiable kernels launch one grid).
-// These kernels run on the ligands' alternative (one atom per lane up to 64
-// atoms) layouts: a launch holds few poses of each ligand.
+// One lane configuration wide enough for every ligand of a handle.  The
+// score and differentiable calls accept a handle whose groups of this width
+// would fit the LDS budget with their pair records staged, as the sampler's
+// have to; their kernels themselves read the records in place, each ligand in
+// its own configuration on its alternative (one atom per lane up to 64
+// atoms) layout.
 static LaneCfg wide_cfg(const dock_ligands_s* L) {
   LaneCfg w{16, 1};
   for (const LigDev& g : L->h_ligs) {
@@ -1020,8 +1022,7 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
   rc = pocket_table(pockets, n_pockets, &tab);
   if (rc) return rc;
   const LaneCfg wc = wide_cfg(L);
-  const int lpp = wc.lpp, apl = wc.apl;
-  if (score_lds_bytes(lpp, apl, L->max_alt_pairs) > 64 * 1024)
+  if (group_lds_bytes(wc.lpp, wc.apl, L->max_alt_pairs) > 64 * 1024)
     return fail(DOCK_E_LIMIT, "pair list too long for the LDS budget");
   ScoreArgs a{};
   a.L = L->arrays();
@@ -1036,13 +1037,18 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
   a.dEdq = dEdq;
   a.xyz = xyz_out;
   a.xyz_stride = xyz_stride;
-  HIP_TRY(launch_score(a, apl == 2, eval_mode(pockets, n_pockets, L), reinterpret_cast<hipStream_t>(stream)));
+  HIP_TRY(launch_score(a, wc.apl == 2, eval_mode(pockets, n_pockets, L), reinterpret_cast<hipStream_t>(stream)));
   return DOCK_OK;
 } catch (...) {
   return exception_status();
 }
 
 // ================================================================ differentiable form
+
+// Poses from which the adjoint with float atomics takes scratch all the same:
+// 2,048 poses of 64 ligands with Vina terms take 272 us with every atomic in
+// dL/dG and dL/dw, 115 through the sums, whose passes cost some 40 us.
+constexpr int64_t kSumPoses = 256;
 
 static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligands_t L, int64_t n_poses,
                       const int32_t* pose_lig, const float* q, int32_t q_stride, const float* xyz,
@@ -1077,8 +1083,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
     a.dLdG[i] = dLdG ? dLdG[i] : nullptr;
   }
   const LaneCfg wc = wide_cfg(L);
-  const int lpp = wc.lpp, apl = wc.apl;
-  if (score_lds_bytes(lpp, apl, L->max_alt_pairs) > 64 * 1024)
+  if (group_lds_bytes(wc.lpp, wc.apl, L->max_alt_pairs) > 64 * 1024)
     return fail(DOCK_E_LIMIT, "pair list too long for the LDS budget");
   a.L = L->arrays();
   a.pockets = tab;
@@ -1096,64 +1101,84 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   a.dLdw = dLdw;
   a.dLdq = dLdq;
   a.dLdx = dLdx;
-  a.max_pairs = L->max_alt_pairs;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (!(dLdE && deterministic)) {
-    HIP_TRY(launch_terms(a, lpp, apl, K, s));
+  const bool two = wc.apl == 2;
+  // dL/dG through per-pocket sums (see Scatter) and dL/dw through per-pose
+  // contributions: always when they have to be repeatable, else from
+  // kSumPoses poses on, unless the stream is being captured, which would
+  // record the scratch allocations.  Scratch is allocated on the stream and
+  // released after the last kernel that reads it.
+  bool want_g = false;
+  GridDev grids[kMaxDiffPockets];
+  for (int i = 0; i < n_pockets; ++i) {
+    grids[i] = pockets[i]->dev.grid;
+    a.unit_off[i + 1] = a.unit_off[i] + (a.dLdG[i] ? adj_units(grids[i]) : 0);
+    want_g |= a.dLdG[i] != nullptr;
+  }
+  bool scratch = dLdE && (want_g || dLdw) && (deterministic || n_poses >= kSumPoses);
+  if (scratch && !deterministic) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    scratch = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  }
+  if (!scratch) {
+    HIP_TRY(launch_terms(a, two, K, s));
     return DOCK_OK;
   }
-  // Deterministic adjoint: dL/dG summed as 64-bit integers (fixed point at a
-  // per-pocket power-of-two scale from a bound on every node's sum), dL/dw as
-  // per-pose contributions reduced in a fixed order.  Scratch is allocated on
-  // the stream and released after the last kernel that reads it.
-  long long off[kMaxDiffPockets + 1] = {0};
-  for (int i = 0; i < n_pockets; ++i) {
-    const GridDev& gd = pockets[i]->dev.grid;
-    const long long n = a.dLdG[i] ? (long long)kTypes * K * gd.dims[0] * gd.dims[1] * gd.dims[2] : 0;
-    off[i + 1] = off[i] + n;
-  }
-  unsigned long long* acc = nullptr;
-  double* scale = nullptr;
-  float* w_pose = nullptr;
-  int* w_pocket = nullptr;
-  hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&scale), sizeof(double) * kMaxDiffPockets, s);
-  if (e == hipSuccess && off[n_pockets] > 0)
-    e = hipMallocAsync(reinterpret_cast<void**>(&acc), sizeof(unsigned long long) * off[n_pockets], s);
-  if (e == hipSuccess && dLdw) {
-    e = hipMallocAsync(reinterpret_cast<void**>(&w_pose), sizeof(float) * size_t(n_poses) * K, s);
-    if (e == hipSuccess) e = hipMallocAsync(reinterpret_cast<void**>(&w_pocket), sizeof(int) * size_t(n_poses), s);
-  }
-  if (e == hipSuccess && acc) e = launch_zero_u64(acc, off[n_pockets], s);
-  if (e == hipSuccess) {
-    AdjBoundArgs b{};
-    b.ligs = L->d_ligs;
-    b.n_ligands = L->n;
-    b.n_pockets = n_pockets;
-    b.K = K;
-    b.n_poses = n_poses;
-    b.pose_lig = pose_lig;
-    b.dLdE = dLdE;
-    b.w = w;
-    b.scale = scale;
-    e = launch_adj_bound(b, s);
+  const bool sums = want_g, per_pose_w = dLdw != nullptr;
+  const long long units = a.unit_off[n_pockets];
+  // one allocation: sums, per-pose contributions, then bounds and flags next
+  // to each other (one clear)
+  a.fixed = deterministic ? K : 0;
+  const auto round16 = [](size_t n) { return (n + 15) / 16 * 16; };
+  const size_t sum_bytes =
+      sums ? size_t(units) * kSumUnit * (a.fixed ? K * sizeof(unsigned long long) : sizeof(float)) : 0;
+  const size_t wp_bytes = per_pose_w ? round16(sizeof(float) * size_t(n_poses) * K) : 0;
+  const size_t wk_bytes = per_pose_w ? round16(sizeof(int) * size_t(n_poses)) : 0;
+  const size_t bound_bytes = sizeof(unsigned) * kBoundWords, flag_words = (bound_bytes + size_t(units) + 3) / 4;
+  unsigned char* mem = nullptr;
+  hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&mem), sum_bytes + wp_bytes + wk_bytes + 4 * flag_words, s);
+  if (e != hipSuccess && !deterministic) {
+    (void)hipGetLastError();  // no memory for the scratch: float atomics
+    a.fixed = 0;
+    HIP_TRY(launch_terms(a, two, K, s));
+    return DOCK_OK;
   }
   if (e == hipSuccess) {
-    for (int i = 0; i < n_pockets; ++i) a.acc[i] = a.dLdG[i] ? acc + off[i] : nullptr;
-    a.acc_scale = scale;
-    a.w_pose = w_pose;
-    a.w_pocket = w_pocket;
-    a.dLdw = dLdw;
-    e = launch_terms(a, lpp, apl, K, s);
+    if (per_pose_w) {
+      a.w_pose = reinterpret_cast<float*>(mem + sum_bytes);
+      a.w_pocket = reinterpret_cast<int*>(mem + sum_bytes + wp_bytes);
+    }
+    if (sums) {
+      a.sum = mem;
+      a.bound = reinterpret_cast<unsigned*>(mem + sum_bytes + wp_bytes + wk_bytes);
+      a.flag = reinterpret_cast<unsigned char*>(a.bound) + bound_bytes;
+      e = launch_fill_u32(a.bound, (long long)flag_words, 0u, s);
+      if (e == hipSuccess) e = launch_adj_mark(a, two, s);
+      if (e == hipSuccess) e = launch_adj_clear(a, s);
+    }
   }
-  for (int i = 0; i < n_pockets && e == hipSuccess; ++i)
-    if (a.dLdG[i]) e = launch_adj_finalize(acc + off[i], scale + i, off[i + 1] - off[i], a.dLdG[i], s);
-  if (e == hipSuccess && dLdw) e = launch_adj_wreduce(w_pose, w_pocket, n_poses, n_pockets, K, dLdw, s);
-  for (void* p : {static_cast<void*>(acc), static_cast<void*>(scale), static_cast<void*>(w_pose),
-                  static_cast<void*>(w_pocket)})
-    if (p) (void)hipFreeAsync(p, s);
+  if (e == hipSuccess) e = launch_terms(a, two, K, s);
+  if (sums && e == hipSuccess) {
+    // all pockets at once unless two of them share (part of) a buffer
+    bool apart = true;
+    for (int i = 0; i < n_pockets; ++i)
+      for (int k = 0; k < i; ++k) {
+        const auto len = [&](int p) {
+          return size_t(kTypes) * K * grids[p].dims[0] * size_t(grids[p].dims[1]) * grids[p].dims[2];
+        };
+        if (a.dLdG[i] && a.dLdG[k] && a.dLdG[i] < a.dLdG[k] + len(k) && a.dLdG[k] < a.dLdG[i] + len(i)) apart = false;
+      }
+    if (apart) {
+      e = launch_adj_expand(a, grids, K, 0, units, s);
+    } else {
+      for (int i = 0; i < n_pockets && e == hipSuccess; ++i)
+        e = launch_adj_expand(a, grids, K, a.unit_off[i], a.unit_off[i + 1], s);
+    }
+  }
+  if (e == hipSuccess && per_pose_w) e = launch_adj_wreduce(a.w_pose, a.w_pocket, n_poses, n_pockets, K, dLdw, s);
+  if (mem) (void)hipFreeAsync(mem, s);
   if (e != hipSuccess)
-    return fail(e == hipErrorOutOfMemory ? DOCK_E_OOM : DOCK_E_HIP,
-                std::string("deterministic adjoint: ") + hipGetErrorString(e));
+    return fail(e == hipErrorOutOfMemory ? DOCK_E_OOM : DOCK_E_HIP, std::string("adjoint: ") + hipGetErrorString(e));
   return DOCK_OK;
 }
 

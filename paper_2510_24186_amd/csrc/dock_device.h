@@ -411,6 +411,7 @@ DK_INLINE uint32_t mul_u24(uint32_t a, uint32_t b) { return (a & 0xffffffu) * (b
 struct Trilerp {
   float v, gx, gy, gz, eout;
   int base;          // flat index of corner (0,0,0)
+  int cx, cy, cz;    // its cell
   float fx, fy, fz;  // cell fractions
 };
 
@@ -441,6 +442,9 @@ DK_INLINE Trilerp trilerp(const float* __restrict__ M, uint64_t first, const Gri
   // dims <= 1024: rows and nodes from full-rate 24-bit products (a 32-bit
   // integer product takes four times as long), node indices below 2^30
   const uint32_t nx = uint32_t(g.dims[0]), nxy = uint32_t(g.dims[0]) * uint32_t(g.dims[1]);
+  t.cx = cx;
+  t.cy = cy;
+  t.cz = cz;
   t.base = int(mul_u24(mul_u24(uint32_t(cz), uint32_t(g.dims[1])) + uint32_t(cy), nx) + uint32_t(cx));
   const float* p0 = M + (first + uint32_t(t.base));
   const float c000 = ldg(p0), c100 = ldg(p0 + 1), c010 = ldg(p0 + nx), c110 = ldg(p0 + nx + 1);
@@ -1310,24 +1314,79 @@ DK_INLINE EvalOut eval_pose(LaneLig<APL>& L, float q, const PocketDev& pk,
   return out;
 }
 
+// Scatter of the adjoint, by bricks of 4 x 2 x 2 nodes whose 16 entries lie
+// next to each other (in 64 bits one L2 line: an atomic whose line is not in
+// L2 brings it in, and that traffic is what the scatter costs); only the
+// bricks near some atom are cleared and read back: unit (t, brick) of a pocket is marked first, from the atoms'
+// positions.  With float atomics the sum is S[t] = sum over atoms of type t of
+// dL/dE times the corner weights, multiplied out afterwards (dL/dG[t][k] = w_k
+// S[t]: 8 atomics per atom instead of 8 K).  In 64-bit fixed point a unit
+// holds K bricks, the contributions of every term.
+constexpr int kSumX = 4, kSumY = 2, kSumZ = 2, kSumUnit = 16;
+struct SumGrid {
+  int nbx, nby, nb;   // bricks per row, rows per slice, bricks
+};
+__host__ __device__ inline SumGrid sum_grid(const GridDev& g) {
+  SumGrid s;
+  s.nbx = (g.dims[0] + kSumX - 1) / kSumX;
+  s.nby = (g.dims[1] + kSumY - 1) / kSumY;
+  s.nb = s.nbx * s.nby * ((g.dims[2] + kSumZ - 1) / kSumZ);
+  return s;
+}
+// offset of a node along each axis inside the brick-ordered array; `unit`:
+// entries per unit
+DK_INLINE size_t sum_x(int unit, int i) { return size_t(i / kSumX) * unit + i % kSumX; }
+DK_INLINE size_t sum_y(const SumGrid& s, int unit, int i) {
+  return size_t(i / kSumY) * s.nbx * unit + i % kSumY * kSumX;
+}
+DK_INLINE size_t sum_z(const SumGrid& s, int unit, int i) {
+  return size_t(i / kSumZ) * s.nbx * s.nby * unit + i % kSumZ * (kSumX * kSumY);
+}
+struct Scatter {
+  float* direct = nullptr;              // float atomics straight into dL/dG, per term
+  float* sum = nullptr;                 // or S of the pocket, float atomics
+  unsigned long long* fixed = nullptr;  // or every term's sum in 64-bit fixed point: integer sums do not
+                                        // depend on their order
+  double scale = 0.0;                   // fixed: 2^(62 - e) (0: a non-finite bound, nothing is added)
+};
+
+// Marks the units that hold a corner of the cell around x, with a margin of a
+// hundredth of a cell (two kernels' positions may differ in the last bits).
+DK_INLINE void mark_units(unsigned char* flag, const SumGrid& sg, const GridDev& g, int type, const float (&x)[3]) {
+  int lo[3], hi[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    float pc, f;
+    bool in;
+    int cell;
+    cell_axis<true>(x[c], g.origin[c], g.hi[c], g.inv_spacing, g.dims[c], pc, in, cell, f);
+    const float u = (pc - g.origin[c]) * g.inv_spacing;
+    lo[c] = min(max(min(int(u - 0.01f), cell), 0), g.dims[c] - 1);
+    hi[c] = min(max(int(u + 0.01f), cell) + 1, g.dims[c] - 1);
+  }
+  for (int z = lo[2] / kSumZ; z <= hi[2] / kSumZ; ++z)
+    for (int y = lo[1] / kSumY; y <= hi[1] / kSumY; ++y)
+      for (int b = lo[0] / kSumX; b <= hi[0] / kSumX; ++b)
+        flag[size_t(type) * sg.nb + (size_t(z) * sg.nby + y) * sg.nbx + b] = 1;
+}
+
 // Differentiable form: the score over per-term maps G[t][k] with weights w
 // (E = sum_k w_k (sum_i trilerp(G[t_i][k], x_i) + sum_pairs phi_k) + E_out),
-// optionally scattering dL/dG for dL/dE = dLdE: into the float maps dLdG by
-// float atomics, or (acc non-null) into 64-bit fixed-point accumulators, each
-// corner weight rounded once to an integer multiple of 1 / acc_scale (a power
-// of two; 0 marks a non-finite bound and drops the scatter).  Integer sums do
-// not depend on the order of the atomics.  Intra-pair forces are summed in
-// LDS as 64-bit fixed point scaled from a bound on the pair forces, which
-// makes them independent of the atomics' order as well.  Atom positions
+// optionally scattering dL/dG for dL/dE = dLdE (see Scatter; in fixed point
+// every corner contribution is rounded once to an integer multiple of 1 /
+// scale, a power of two).  Intra-pair forces are gathered in
+// a fixed order and summed in FP64 (pass layout) or summed in LDS as 64-bit
+// fixed point scaled from a bound on the pair forces, so they do not depend
+// on timing either.  ADJ: false for the energy alone (no scatter, no
+// forces).  `pairs`: the ligand's records in global memory.  Atom positions
 // come from FK of q (XIN = false) or are given (XIN = true).  Leaves
 // per-atom gradients in g, per-term sums (reduced over the group) in ek, and
 // returns E.
-template <int LPP, int APL, int K, bool XIN>
+template <int LPP, int APL, int K, bool XIN, bool ADJ>
 DK_INLINE float eval_terms(const LaneLig<APL>& L, float q, float (&x)[APL][3], float (&g)[APL][3],
                            Rigid& rg, const float* __restrict__ G, const GridDev& grid,
                            const float (&w)[K], const PairRec* __restrict__ pairs, const GroupSlab& S,
-                           int r, float dLdE, float* __restrict__ dLdG, float (&ek)[K],
-                           unsigned long long* __restrict__ acc = nullptr, double acc_scale = 0.0) {
+                           int r, float dLdE, const Scatter& sc, float (&ek)[K]) {
   if (!XIN) rg = fk_place<LPP, APL>(L, q, r, x, S.xs);
   const size_t nxyz = size_t(grid.dims[0]) * grid.dims[1] * grid.dims[2];
   const int nx = grid.dims[0], nxy = grid.dims[0] * grid.dims[1];
@@ -1360,99 +1419,177 @@ DK_INLINE float eval_terms(const LaneLig<APL>& L, float q, float (&x)[APL][3], f
           g[s][1] += sy;
           g[s][2] += sz;
         }
-        if (dLdG || acc) {
-          const size_t off = size_t(L.atype[s] * K + k) * nxyz + tl.base;
-          const float c = dLdE * w[k];
+        auto corners = [&](float c, float (&cv)[8]) {
           const float fx = tl.fx, fy = tl.fy, fz = tl.fz;
-          const float cv[8] = {c * (1.f - fx) * (1.f - fy) * (1.f - fz), c * fx * (1.f - fy) * (1.f - fz),
-                               c * (1.f - fx) * fy * (1.f - fz),         c * fx * fy * (1.f - fz),
-                               c * (1.f - fx) * (1.f - fy) * fz,         c * fx * (1.f - fy) * fz,
-                               c * (1.f - fx) * fy * fz,                 c * fx * fy * fz};
+          cv[0] = c * (1.f - fx) * (1.f - fy) * (1.f - fz);
+          cv[1] = c * fx * (1.f - fy) * (1.f - fz);
+          cv[2] = c * (1.f - fx) * fy * (1.f - fz);
+          cv[3] = c * fx * fy * (1.f - fz);
+          cv[4] = c * (1.f - fx) * (1.f - fy) * fz;
+          cv[5] = c * fx * (1.f - fy) * fz;
+          cv[6] = c * (1.f - fx) * fy * fz;
+          cv[7] = c * fx * fy * fz;
+        };
+        if (ADJ && sc.direct) {
+          float* dst = sc.direct + size_t(L.atype[s] * K + k) * nxyz + tl.base;
+          float cv[8];
+          corners(dLdE * w[k], cv);
           const size_t co[8] = {0, 1, size_t(nx), size_t(nx) + 1, size_t(nxy), size_t(nxy) + 1,
                                 size_t(nxy) + nx, size_t(nxy) + nx + 1};
-          if (acc) {
-            if (acc_scale > 0.0) {
 #pragma unroll
-              for (int cn = 0; cn < 8; ++cn)
-                atomicAdd(acc + off + co[cn],
-                          static_cast<unsigned long long>(__double2ll_rn(double(cv[cn]) * acc_scale)));
-            }
-          } else {
+          for (int cn = 0; cn < 8; ++cn) atomicAdd(dst + co[cn], cv[cn]);
+        }
+        if (ADJ && ((k == 0 && sc.sum) || (sc.fixed && sc.scale > 0.0))) {
+          const SumGrid sg = sum_grid(grid);
+          const int unit = sc.fixed ? K * kSumUnit : kSumUnit;
+          float cv[8];
+          corners(sc.fixed ? dLdE * w[k] : dLdE, cv);
+          const size_t t0 = size_t(L.atype[s]) * sg.nb * unit + k * kSumUnit;
+          const size_t ox[2] = {t0 + sum_x(unit, tl.cx), t0 + sum_x(unit, tl.cx + 1)};
+          const size_t oy[2] = {sum_y(sg, unit, tl.cy), sum_y(sg, unit, tl.cy + 1)};
+          const size_t oz[2] = {sum_z(sg, unit, tl.cz), sum_z(sg, unit, tl.cz + 1)};
 #pragma unroll
-            for (int cn = 0; cn < 8; ++cn) atomicAdd(dLdG + off + co[cn], cv[cn]);
+          for (int cn = 0; cn < 8; ++cn) {
+            const size_t at = ox[cn & 1] + oy[cn >> 1 & 1] + oz[cn >> 2];
+            if (sc.fixed)
+              atomicAdd(sc.fixed + at, static_cast<unsigned long long>(__double2ll_rn(double(cv[cn]) * sc.scale)));
+            else
+              atomicAdd(sc.sum + at, cv[cn]);
           }
         }
       }
       S.xs[atom] = make_float4(x[s][0], x[s][1], x[s][2], 0.f);
-      S.fx[atom] = 0.0;
-      S.fy[atom] = 0.0;
-      S.fz[atom] = 0.0;
     }
   }
   wave_sync();
-  // The force slots (zeroed above as 0.0, i.e. integer 0) hold fixed-point
-  // sums.  An atom takes at most 127 pair forces, each at most
-  // sum_k |w_k| D_k in magnitude, with D_k >= max |d phi_k / dd| over
-  // d >= 0.1 (below 0.1 the clash term is flat): TRIDS 1/sqrt(2e), 1/0.1,
-  // 2 * 0.3/0.18 * e^-1/2; Vina sqrt(8) e^-1/2, 1/sqrt(2e), 2 * 3.8, 1,
-  // 1/0.7, each rounded up.  The scale 2^(62 - e) with 127 sum_k |w_k| D_k
-  // <= 2^e keeps every sum inside the signed 64-bit range.
-  unsigned long long* fxi = reinterpret_cast<unsigned long long*>(S.fx);
-  unsigned long long* fyi = reinterpret_cast<unsigned long long*>(S.fy);
-  unsigned long long* fzi = reinterpret_cast<unsigned long long*>(S.fz);
-  double force_fix = 0.0, force_unfix = 0.0;
-  {
-    constexpr float kD3[3] = {0.5f, 10.0f, 2.1f};
-    constexpr float kD5[5] = {1.8f, 0.5f, 8.0f, 1.0f, 1.5f};
-    double fb = 0.0;
+  // A bound on an atom's pair forces: each is at most sum_k |w_k| D_k in
+  // magnitude, with D_k >= max |d phi_k / dd| over d >= 0.1 (below 0.1 the
+  // clash term is flat): TRIDS 1/sqrt(2e), 1/0.1, 2 * 0.3/0.18 * e^-1/2; Vina
+  // sqrt(8) e^-1/2, 1/sqrt(2e), 2 * 3.8, 1, 1/0.7, each rounded up.  Without
+  // a finite one (non-finite weights) the intra forces drop out.
+  constexpr float kD3[3] = {0.5f, 10.0f, 2.1f};
+  constexpr float kD5[5] = {1.8f, 0.5f, 8.0f, 1.0f, 1.5f};
+  double fbound = 0.0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) fb += fabs(double(w[k])) * double(K == 3 ? kD3[k % 3] : kD5[k % 5]);
-    if (fb < 1e300) {  // finite weights (else the intra forces drop out)
-      int ex = 0;
-      (void)frexp(127.0 * fb, &ex);
-      force_fix = ldexp(1.0, 62 - ex);
-      force_unfix = ldexp(1.0, ex - 62);
-    }
-  }
-  const int pstep = L.n_pass > 0 ? 2 : 1;
-  for (int p = r; p < L.n_prec; p += LPP) {
-    const PairRec pr = pairs[pstep * p];
-    if (pr.w & kPairEmpty) continue;
-    const int i = pr.w & 0xff, j = (pr.w >> 8) & 0xff;
-    const f32x4_t xi = lds_read4(lds_addr(S.xs + i)), xj = lds_read4(lds_addr(S.xs + j));
+  for (int k = 0; k < K; ++k) fbound += fabs(double(w[k])) * double(K == 3 ? kD3[k % 3] : kD5[k % 5]);
+  const bool finite_w = fbound < 1e300;
+  // per-term energies of one pair into el; the force on its first atom
+  auto pair = [&](uint32_t word, float rsum, const f32x4_t& xi, const f32x4_t& xj, float (&f)[3]) {
+    f[0] = f[1] = f[2] = 0.f;
     const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
     const float d2 = dx * dx + dy * dy + dz * dz;
     const float d = sqrtf(d2);
     float v[K], dv[K];
-    pair_terms_f32<K>(d2, d, pr.rsum, pr.w >> 24, v, dv);
+    pair_terms_f32<K>(d2, d, rsum, word >> 24, v, dv);
     float de = 0.f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       el[k] += v[k];
       de += w[k] * dv[k];
     }
-    if (de != 0.f && d > 0.f) {
-      const float c = de / d;
-      const long long ix = __double2ll_rn(double(c * dx) * force_fix),
-                      iy = __double2ll_rn(double(c * dy) * force_fix),
-                      iz = __double2ll_rn(double(c * dz) * force_fix);
-      atomicAdd(&fxi[i], static_cast<unsigned long long>(ix));
-      atomicAdd(&fyi[i], static_cast<unsigned long long>(iy));
-      atomicAdd(&fzi[i], static_cast<unsigned long long>(iz));
-      atomicAdd(&fxi[j], static_cast<unsigned long long>(-ix));
-      atomicAdd(&fyi[j], static_cast<unsigned long long>(-iy));
-      atomicAdd(&fzi[j], static_cast<unsigned long long>(-iz));
-    }
-  }
-  wave_sync();
+    if (!ADJ || !(de != 0.f && d > 0.f) || !finite_w) return;
+    const float c = de / d;
+    f[0] = c * dx;
+    f[1] = c * dy;
+    f[2] = c * dz;
+  };
+  if (L.n_pass > 0 && L.pass_apl == APL && (APL == 1 || L.pass_w == LPP)) {
+    // ---- pass layout (see eval_pose): forces stored per slot and gathered
+    // per atom in a fixed order, summed in FP64
+    const int W = L.pass_w, cap = L.pull_cap;
+    const bool slot_lane = r < W;
+    const uint32_t lane_slot = slot_lane ? uint32_t(r) : 0u;
+    const uint32_t xs_a = lds_addr(S.xs), fb_a = lds_addr(S.fb);
+    if (ADJ && r == 0) lds_write4(fb_a + 16u * uint32_t(W), 0.f, 0.f, 0.f);
+    double fsum[APL][3] = {};
+    auto run_passes = [&](auto cap_c) {
+      constexpr int CAP = decltype(cap_c)::value;
+      constexpr bool kTwoWords = APL * CAP == 8;
+      const PairRec* rp = pairs + 2 * lane_slot;
+      const uint32_t* wp = reinterpret_cast<const uint32_t*>(pairs + 2 * size_t(L.n_prec)) + lane_slot;
+      uint4 rec = ldg_u4(rp);
+      uint32_t w1 = ADJ && kTwoWords ? ldg(wp) : 0u;
+      for (int ps = 0; ps < L.n_pass; ++ps) {
+        if (ps + 1 < L.n_pass) {
+          rp += 2 * W;
+          wp += W;
+        }
+        const uint4 nxt = ldg_u4(rp);
+        const uint32_t nxt_w1 = ADJ && kTwoWords ? ldg(wp) : 0u;
+        float f[3] = {0.f, 0.f, 0.f};
+        const f32x4_t xi = lds_read4(lds_entry16<0>(rec.x, xs_a)), xj = lds_read4(lds_entry16<1>(rec.x, xs_a));
+        if (slot_lane && !(rec.x & kPairEmpty)) pair(rec.x, __uint_as_float(rec.y), xi, xj, f);
+        if (ADJ) {
+          if (slot_lane) lds_write4(fb_a + 16u * uint32_t(r), f[0], f[1], f[2]);
+          wave_sync();
+          uint32_t ad[APL][CAP];
+          gather_addresses<APL, CAP>(rec.w, w1, fb_a, ad);
+          gather_forces<APL, CAP>(ad, fsum, [] {});
+          wave_sync();
+        }
+        rec = nxt;
+        w1 = nxt_w1;
+      }
+    };
+    if (!ADJ || (APL == 1 && cap == 4))
+      run_passes(std::integral_constant<int, 4>{});
+    else if (APL == 2 && cap == 2)
+      run_passes(std::integral_constant<int, 2>{});
+    else
+      run_passes(std::integral_constant<int, APL == 2 ? 4 : 8>{});
 #pragma unroll
-  for (int s = 0; s < APL; ++s) {
-    const int atom = APL * r + s;
-    if (atom < L.n_atoms) {
-      g[s][0] += float(double(static_cast<long long>(fxi[atom])) * force_unfix);
-      g[s][1] += float(double(static_cast<long long>(fyi[atom])) * force_unfix);
-      g[s][2] += float(double(static_cast<long long>(fzi[atom])) * force_unfix);
+    for (int s = 0; s < APL; ++s)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) g[s][k] += APL * r + s < L.n_atoms ? float(fsum[s][k]) : 0.f;
+  } else {
+    // ---- strided: forces as 64-bit fixed point in LDS.  An atom takes at
+    // most 127 of them; the scale 2^(62 - e) with 127 fbound <= 2^e keeps every
+    // sum inside the signed 64-bit range.
+    unsigned long long* fxi = reinterpret_cast<unsigned long long*>(S.fx);
+    unsigned long long* fyi = reinterpret_cast<unsigned long long*>(S.fy);
+    unsigned long long* fzi = reinterpret_cast<unsigned long long*>(S.fz);
+    double force_fix = 0.0, force_unfix = 0.0;
+    if (finite_w) {
+      int ex = 0;
+      (void)frexp(127.0 * fbound, &ex);
+      force_fix = ldexp(1.0, 62 - ex);
+      force_unfix = ldexp(1.0, ex - 62);
     }
+    if (ADJ)
+#pragma unroll
+      for (int s = 0; s < APL; ++s)
+        if (APL * r + s < L.n_atoms) fxi[APL * r + s] = fyi[APL * r + s] = fzi[APL * r + s] = 0ull;
+    wave_sync();
+    const int pstep = L.n_pass > 0 ? 2 : 1;
+    for (int p = r; p < L.n_prec; p += LPP) {
+      const PairRec pr = ldg(pairs + pstep * p);
+      if (pr.w & kPairEmpty) continue;
+      const int i = pr.w & 0xff, j = (pr.w >> 8) & 0xff;
+      const f32x4_t xi = lds_read4(lds_addr(S.xs + i)), xj = lds_read4(lds_addr(S.xs + j));
+      float f[3];
+      pair(pr.w, pr.rsum, xi, xj, f);
+      if (ADJ && (f[0] != 0.f || f[1] != 0.f || f[2] != 0.f)) {
+        const long long ix = __double2ll_rn(double(f[0]) * force_fix), iy = __double2ll_rn(double(f[1]) * force_fix),
+                        iz = __double2ll_rn(double(f[2]) * force_fix);
+        atomicAdd(&fxi[i], static_cast<unsigned long long>(ix));
+        atomicAdd(&fyi[i], static_cast<unsigned long long>(iy));
+        atomicAdd(&fzi[i], static_cast<unsigned long long>(iz));
+        atomicAdd(&fxi[j], static_cast<unsigned long long>(-ix));
+        atomicAdd(&fyi[j], static_cast<unsigned long long>(-iy));
+        atomicAdd(&fzi[j], static_cast<unsigned long long>(-iz));
+      }
+    }
+    wave_sync();
+    if (ADJ)
+#pragma unroll
+      for (int s = 0; s < APL; ++s) {
+        const int atom = APL * r + s;
+        if (atom < L.n_atoms) {
+          g[s][0] += float(double(static_cast<long long>(fxi[atom])) * force_unfix);
+          g[s][1] += float(double(static_cast<long long>(fyi[atom])) * force_unfix);
+          g[s][2] += float(double(static_cast<long long>(fzi[atom])) * force_unfix);
+        }
+      }
   }
   float E = group_sum<LPP>(eout);
 #pragma unroll

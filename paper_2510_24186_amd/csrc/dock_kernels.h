@@ -36,6 +36,8 @@ struct ScoreArgs {
 };
 
 constexpr int kMaxDiffPockets = 16;
+constexpr int kBoundSlots = 32;
+constexpr int kBoundWords = kMaxDiffPockets * (1 + kBoundSlots);
 
 struct TermsArgs {
   LigandArrays L;
@@ -55,36 +57,37 @@ struct TermsArgs {
   float* dLdw;
   float* dLdq;
   float* dLdx;
-  int max_pairs;
-  // deterministic adjoint (null otherwise): dL/dG into 64-bit fixed-point
-  // accumulators acc[pocket] (layout of dLdG) at scale acc_scale[pocket];
-  // dL/dw as per-pose contributions w_pose [n_poses * K] and the pose's
-  // pocket w_pocket [n_poses] (-1: invalid ligand), reduced afterwards
-  unsigned long long* acc[kMaxDiffPockets];
-  const double* acc_scale;
+  int chunk;                         // poses per wavefront
+  // dL/dG through per-pocket sums (null: float atomics into dLdG): flags of
+  // the units, the sums (floats, one brick per unit; or, when fixed = K, 64-bit
+  // fixed point, K bricks per unit), the first unit of each pocket (no units:
+  // no dL/dG wanted), and for the fixed-point scale the largest |dLdE| * atoms
+  // of a pocket's poses (FP32 bits): bound[pocket], after launch_adj_clear,
+  // from kBoundSlots slots per pocket behind
+  unsigned char* flag;
+  void* sum;
+  int fixed;
+  long long unit_off[kMaxDiffPockets + 1];
+  unsigned* bound;
+  // dL/dw in a fixed order (null: float atomics): per-pose contributions
+  // w_pose [n_poses * K] and the pose's pocket w_pocket [n_poses] (-1: invalid
+  // ligand), reduced afterwards
   float* w_pose;
   int* w_pocket;
 };
 
-// Deterministic adjoint helpers.
-struct AdjBoundArgs {
-  const LigDev* ligs;
-  int n_ligands, n_pockets, K;
-  long long n_poses;
-  const int* pose_lig;
-  const float* dLdE;
-  const float* w;       // [n_pockets * K]
-  double* scale;        // out [n_pockets]: 2^(62 - e), 0 for a non-finite bound
-};
-hipError_t launch_adj_bound(const AdjBoundArgs& a, hipStream_t s);
-// dLdG[i] += acc[i] / scale (NaN where scale = 0), i < n
-hipError_t launch_adj_finalize(const unsigned long long* acc, const double* scale, long long n, float* dLdG,
-                               hipStream_t s);
+// The passes around launch_terms when a.sum is set: units marked (flag and
+// bound cleared by the caller), the marked units' sums cleared, and after
+// launch_terms the units [u0, u1) added to dLdG.
+hipError_t launch_adj_mark(TermsArgs a, bool two_per_lane, hipStream_t s);
+hipError_t launch_adj_clear(const TermsArgs& a, hipStream_t s);
+hipError_t launch_adj_expand(const TermsArgs& a, const GridDev* grids, int K, long long u0, long long u1, hipStream_t s);
+// units of a pocket
+long long adj_units(const GridDev& g);
 // dLdw[pi * K + k] += sum over poses p with w_pocket[p] == pi of w_pose[p * K + k],
 // in a fixed order
 hipError_t launch_adj_wreduce(const float* w_pose, const int* w_pocket, long long n_poses, int n_pockets, int K,
                               float* dLdw, hipStream_t s);
-hipError_t launch_zero_u64(unsigned long long* p, long long n, hipStream_t s);
 
 struct SampleArgs {
   LigandArrays L;
@@ -160,7 +163,8 @@ hipError_t launch_map_adjoint(const MapAdjArgs& a, hipStream_t s);
 
 // LDS bytes a sampler block of `block` threads needs.
 size_t sample_lds_bytes(int lpp, int apl, int block, int max_pairs);
-size_t score_lds_bytes(int lpp, int apl, int max_pairs);
+// LDS of the groups of one wavefront with their pair records.
+size_t group_lds_bytes(int lpp, int apl, int max_pairs);
 
 hipError_t launch_map_build(const MapArgs& a, hipStream_t s);
 // mode: 0 grid maps, 1 direct pair sums, 2 grid maps + E_MDN
@@ -183,7 +187,7 @@ struct RankArgs {
   int* out_idx;
 };
 hipError_t launch_rank(const RankArgs& a, hipStream_t s);
-hipError_t launch_terms(const TermsArgs& a, int lpp, int apl, int K, hipStream_t s);
+hipError_t launch_terms(TermsArgs a, bool two_per_lane, int K, hipStream_t s);
 hipError_t launch_philox(const uint32_t* ctr, uint32_t k0, uint32_t k1, long long n, uint32_t* out,
                          hipStream_t s);
 hipError_t launch_fill_int(int* p, int n, int v, hipStream_t s);

@@ -458,12 +458,11 @@ constexpr size_t slab_bytes(int lpp, int apl) {
          (size_t(lpp) * apl * 24 > size_t(lpp) * 32 + 16 ? size_t(lpp) * apl * 24 : size_t(lpp) * 32 + 16);
 }
 // staged pair entries (8 bytes each), padded so the float4 slab that follows
-// is aligned
+// is aligned (sampler)
 constexpr size_t pair_bytes(int max_pairs) { return (size_t(max_pairs) * 8 + 15) / 16 * 16; }
 
-size_t score_lds_bytes(int lpp, int apl, int max_pairs) {
-  const int gpb = 64 / lpp;
-  return size_t(gpb) * (pair_bytes(max_pairs) + slab_bytes(lpp, apl));
+size_t group_lds_bytes(int lpp, int apl, int max_pairs) {
+  return size_t(64 / lpp) * (pair_bytes(max_pairs) + slab_bytes(lpp, apl));
 }
 
 size_t sample_lds_bytes(int lpp, int apl, int block, int max_pairs) {
@@ -617,16 +616,30 @@ hipError_t launch_score(ScoreArgs a, bool two_per_lane, int mode, hipStream_t s)
 
 // ================================================================ differentiable form
 
-template <int LPP, int APL, int K, bool XIN>
-__global__ void __launch_bounds__(64) terms_kernel(TermsArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int GPB = 64 / LPP;
+// Fixed-point scale of a pocket's sums: 2^(62 - e) with 2^e >= B = n_poses *
+// max_p(|dLdE_p| N_p) * max_k |w_k|, a bound on any node's |dL/dG| (an atom's
+// eight corner weights are non-negative and sum to one); 0 where B is not
+// finite.  Maxima do not depend on the order of evaluation.
+DK_INLINE double fixed_scale(const TermsArgs& a, int pi, int K) {
+  float mw = 0.f;
+  for (int k = 0; k < K; ++k) {
+    const float v = fabsf(a.w[pi * K + k]);
+    mw = fmaxf(mw, v <= FLT_MAX ? v : INFINITY);
+  }
+  const double B = double(a.n_poses) * double(__uint_as_float(a.bound[pi])) * double(mw);
+  if (!(B <= DBL_MAX)) return 0.0;
+  if (!(B > 0.0)) return 1.0;
+  int ex = 0;
+  (void)frexp(B, &ex);
+  return ldexp(1.0, 62 - ex);
+}
+
+template <int LPP, int APL, int K, bool XIN, bool ADJ>
+DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* smem) {
   const int grp = threadIdx.x / LPP, r = threadIdx.x % LPP;
-  const long long pose = (long long)blockIdx.x * GPB + grp;
-  unsigned char* mine = smem + size_t(grp) * (pair_bytes(a.max_pairs) + slab_bytes(LPP, APL));
-  PairRec* gp = reinterpret_cast<PairRec*>(mine);
-  const GroupSlab S = make_slab<LPP, APL>(mine + pair_bytes(a.max_pairs));
+  const long long pose = first + grp;
   if (pose >= a.n_poses) return;
+  const GroupSlab S = make_slab<LPP, APL>(smem + size_t(grp) * slab_bytes(LPP, APL));
   const int lig = a.pose_lig[pose];
   if (lig < 0 || lig >= a.n_ligands) {
     if (r == 0 && a.E) a.E[pose] = __int_as_float(0x7fc00000);
@@ -642,8 +655,6 @@ __global__ void __launch_bounds__(64) terms_kernel(TermsArgs a) {
   float w[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) w[k] = a.w[pi * K + k];
-  for (int p = r; p < lg.n_stage; p += LPP) gp[p] = a.L.pairs[lg.pair_off + p];
-  wave_sync();
   float q = 0.f;
   float x[APL][3], g[APL][3], ek[K];
   Rigid rg{};
@@ -659,14 +670,23 @@ __global__ void __launch_bounds__(64) terms_kernel(TermsArgs a) {
   } else {
     q = r < lg.n_dof ? a.q[pose * a.q_stride + r] : 0.f;
   }
-  const float dLdE = a.dLdE ? a.dLdE[pose] : 0.f;
-  const bool det = a.acc_scale != nullptr;
-  const float E = eval_terms<LPP, APL, K, XIN>(L, q, x, g, rg, a.G[pi], pk.grid, w, gp, S, r, dLdE,
-                                               (a.dLdE && !det) ? a.dLdG[pi] : nullptr, ek,
-                                               (a.dLdE && det) ? a.acc[pi] : nullptr,
-                                               det ? a.acc_scale[pi] : 0.0);
+  const float dLdE = ADJ ? a.dLdE[pose] : 0.f;
+  Scatter sc;
+  if (ADJ && a.dLdG[pi]) {
+    const size_t at = size_t(a.unit_off[pi]) * kSumUnit;
+    if (!a.sum) {
+      sc.direct = a.dLdG[pi];
+    } else if (a.fixed) {
+      sc.fixed = static_cast<unsigned long long*>(a.sum) + at * K;
+      sc.scale = fixed_scale(a, pi, K);
+    } else {
+      sc.sum = static_cast<float*>(a.sum) + at;
+    }
+  }
+  const float E = eval_terms<LPP, APL, K, XIN, ADJ>(L, q, x, g, rg, a.G[pi], pk.grid, w, a.L.pairs + lg.pair_off, S,
+                                                    r, dLdE, sc, ek);
   if (r == 0 && a.E) a.E[pose] = E;
-  if (!a.dLdE) return;
+  if (!ADJ) return;
   if (r == 0 && a.w_pose) {
 #pragma unroll
     for (int k = 0; k < K; ++k) a.w_pose[pose * K + k] = dLdE * ek[k];
@@ -693,120 +713,264 @@ __global__ void __launch_bounds__(64) terms_kernel(TermsArgs a) {
   }
 }
 
-template <int K, bool XIN>
-static hipError_t launch_terms_k(const TermsArgs& a, int lpp, int apl, unsigned blocks, size_t lds,
-                                 hipStream_t s) {
-  if (lpp == 16 && apl == 1)
-    hipLaunchKernelGGL((terms_kernel<16, 1, K, XIN>), dim3(blocks), dim3(64), lds, s, a);
-  else if (lpp == 32 && apl == 1)
-    hipLaunchKernelGGL((terms_kernel<32, 1, K, XIN>), dim3(blocks), dim3(64), lds, s, a);
-  else if (lpp == 64 && apl == 1)
-    hipLaunchKernelGGL((terms_kernel<64, 1, K, XIN>), dim3(blocks), dim3(64), lds, s, a);
-  else
-    hipLaunchKernelGGL((terms_kernel<64, 2, K, XIN>), dim3(blocks), dim3(64), lds, s, a);
-  return hipGetLastError();
+// The adjoint holds two waves per SIMD without spills (three spill 49
+// registers: 16 pockets x 4,096 poses 534 us the call, two 521); the energy
+// alone four.  The gathers from the per-term maps and the scatter's lines,
+// both beyond L2, bound them.
+template <int K, bool XIN, bool ADJ>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ADJ ? 2 : 4))) terms_kernel(TermsArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const long long base = (long long)blockIdx.x * a.chunk;
+  const int n = int(min((long long)a.chunk, a.n_poses - base));
+  int cfg = 0;
+  if (int(threadIdx.x) < n) {
+    const int lig = a.pose_lig[base + threadIdx.x];
+    if (lig >= 0 && lig < a.n_ligands) cfg = lane_config(a.L.ligs + lig);
+  }
+  for (int at = 0; at < n;) {
+    const WaveForm f = next_form(cfg, at, n);
+    if (f.lanes == 16)
+      terms_poses<16, 1, K, XIN, ADJ>(a, base + at, smem);
+    else if (f.lanes == 32)
+      terms_poses<32, 1, K, XIN, ADJ>(a, base + at, smem);
+    else if (f.lanes == 64)
+      terms_poses<64, 1, K, XIN, ADJ>(a, base + at, smem);
+    else
+      terms_poses<64, 2, K, XIN, ADJ>(a, base + at, smem);
+    wave_sync();
+    at += f.poses;
+  }
 }
 
-hipError_t launch_terms(const TermsArgs& a, int lpp, int apl, int K, hipStream_t s) {
-  const int gpb = 64 / lpp;
-  const unsigned blocks = unsigned((a.n_poses + gpb - 1) / gpb);
-  const size_t lds = score_lds_bytes(lpp, apl, a.max_pairs);
-  if (blocks == 0) return hipSuccess;
-  const bool xin = a.xyz != nullptr;
-  if (K == 3) return xin ? launch_terms_k<3, true>(a, lpp, apl, blocks, lds, s)
-                         : launch_terms_k<3, false>(a, lpp, apl, blocks, lds, s);
-  return xin ? launch_terms_k<5, true>(a, lpp, apl, blocks, lds, s)
-             : launch_terms_k<5, false>(a, lpp, apl, blocks, lds, s);
+hipError_t launch_terms(TermsArgs a, bool two_per_lane, int K, hipStream_t s) {
+  if (a.n_poses <= 0) return hipSuccess;
+  a.chunk = wave_chunk(a.n_poses);
+  const unsigned blocks = unsigned((a.n_poses + a.chunk - 1) / a.chunk);
+  const size_t lds = wave_slab_bytes(two_per_lane);
+  const bool xin = a.xyz != nullptr, adj = a.dLdE != nullptr;
+#define X(KK, XI, AD)                                                                              \
+  if (K == KK && xin == XI && adj == AD) {                                                         \
+    hipLaunchKernelGGL((terms_kernel<KK, XI, AD>), dim3(blocks), dim3(64), lds, s, a);             \
+    return hipGetLastError();                                                                      \
+  }
+  X(3, false, false) X(3, false, true) X(3, true, false) X(3, true, true)
+  X(5, false, false) X(5, false, true) X(5, true, false) X(5, true, true)
+#undef X
+  return hipErrorInvalidValue;
 }
 
 // ================================================================ deterministic adjoint
 
-// One workgroup: per pocket, the bound B = n_poses * max_p(|dLdE_p| N_p) *
-// max_k |w_k| on any node's |dL/dG| (each atom's eight corner weights are
-// non-negative and sum to one), and the fixed-point scale 2^(62 - e) with
-// B <= 2^e.  Maxima do not depend on the order of evaluation.
-__global__ void __launch_bounds__(256) adj_bound_kernel(AdjBoundArgs a) {
-  __shared__ float red[kMaxDiffPockets][256];
-  float m[kMaxDiffPockets];
-#pragma unroll
-  for (int k = 0; k < kMaxDiffPockets; ++k) m[k] = 0.f;
-  for (long long p = threadIdx.x; p < a.n_poses; p += 256) {
-    const int lig = a.pose_lig[p];
-    if (lig < 0 || lig >= a.n_ligands) continue;
-    const LigDev& lg = a.ligs[lig];
-    float v = fabsf(a.dLdE[p]) * float(lg.n_atoms);
+// Marks the units of S that the poses' atoms reach, and takes the bound of
+// the fixed-point scale along: a pose per group, its forward kinematics only.
+template <int LPP, int APL, bool XIN>
+DK_INLINE void mark_poses(const TermsArgs& a, long long first, unsigned char* smem) {
+  const int grp = threadIdx.x / LPP, r = threadIdx.x % LPP;
+  const long long pose = first + grp;
+  if (pose >= a.n_poses) return;
+  const int lig = a.pose_lig[pose];
+  if (lig < 0 || lig >= a.n_ligands) return;
+  const GroupSlab S = make_slab<LPP, APL>(smem + size_t(grp) * slab_bytes(LPP, APL));
+  const LigDev lg = a.L.ligs[lig];
+  const int pi = lg.pocket;
+  if (!a.dLdG[pi]) return;
+  if (r == 0 && a.fixed) {
+    float v = fabsf(a.dLdE[pose]) * float(lg.n_atoms);
     if (!(v <= FLT_MAX)) v = INFINITY;  // NaN counts as unbounded
-#pragma unroll
-    for (int k = 0; k < kMaxDiffPockets; ++k)
-      if (k == lg.pocket) m[k] = fmaxf(m[k], v);
+    // by slots: atomics on one address take their turns
+    atomicMax(&a.bound[kMaxDiffPockets + pi * kBoundSlots + int(pose) % kBoundSlots], __float_as_uint(v));
   }
+  const PocketDev pk = a.pockets[pi];
+  LaneLig<APL> L;
+  load_lane_lig<LPP, APL>(L, lg, a.L.ligs + lig, a.L.atoms, a.L.frags, a.L.tors, pk, r);
+  float x[APL][3];
+  if (XIN) {
 #pragma unroll
-  for (int k = 0; k < kMaxDiffPockets; ++k) red[k][threadIdx.x] = m[k];
+    for (int s = 0; s < APL; ++s) {
+      const float* src = a.xyz + pose * a.xyz_stride + 3 * L.aorig[s];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) x[s][c] = APL * r + s < lg.n_atoms ? src[c] : 0.f;
+    }
+  } else {
+    const float q = r < lg.n_dof ? a.q[pose * a.q_stride + r] : 0.f;
+    (void)fk_place<LPP, APL>(L, q, r, x, S.xs);
+  }
+  const SumGrid sg = sum_grid(pk.grid);
+#pragma unroll
+  for (int s = 0; s < APL; ++s)
+    if (APL * r + s < lg.n_atoms) mark_units(a.flag + a.unit_off[pi], sg, pk.grid, L.atype[s], x[s]);
+}
+
+template <bool XIN>
+__global__ void __launch_bounds__(64) adj_mark_kernel(TermsArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const long long base = (long long)blockIdx.x * a.chunk;
+  const int n = int(min((long long)a.chunk, a.n_poses - base));
+  int cfg = 0;
+  if (int(threadIdx.x) < n) {
+    const int lig = a.pose_lig[base + threadIdx.x];
+    if (lig >= 0 && lig < a.n_ligands) cfg = lane_config(a.L.ligs + lig);
+  }
+  for (int at = 0; at < n;) {
+    const WaveForm f = next_form(cfg, at, n);
+    if (f.lanes == 16)
+      mark_poses<16, 1, XIN>(a, base + at, smem);
+    else if (f.lanes == 32)
+      mark_poses<32, 1, XIN>(a, base + at, smem);
+    else if (f.lanes == 64)
+      mark_poses<64, 1, XIN>(a, base + at, smem);
+    else
+      mark_poses<64, 2, XIN>(a, base + at, smem);
+    wave_sync();
+    at += f.poses;
+  }
+}
+
+hipError_t launch_adj_mark(TermsArgs a, bool two_per_lane, hipStream_t s) {
+  if (a.n_poses <= 0) return hipSuccess;
+  a.chunk = wave_chunk(a.n_poses);
+  const unsigned blocks = unsigned((a.n_poses + a.chunk - 1) / a.chunk);
+  const size_t lds = wave_slab_bytes(two_per_lane);
+  if (a.xyz)
+    hipLaunchKernelGGL(adj_mark_kernel<true>, dim3(blocks), dim3(64), lds, s, a);
+  else
+    hipLaunchKernelGGL(adj_mark_kernel<false>, dim3(blocks), dim3(64), lds, s, a);
+  return hipGetLastError();
+}
+
+long long adj_units(const GridDev& g) { return (long long)kTypes * sum_grid(g).nb; }
+
+// Calls f(unit, entry) for every marked unit of [u0, u1) (all of them where
+// all(unit) says so), each with 16 lanes: a wave looks at 32 flags, then takes
+// the marked ones four at a time.
+constexpr int kFlagsPerWave = 32;
+template <class All, class F>
+DK_INLINE void for_marked_units(const unsigned char* flag, long long u0, long long u1, All&& all, F&& f) {
+  const int lane = threadIdx.x & 63, grp = lane / kSumUnit;
+  const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / 64,
+                  n_waves = (long long)gridDim.x * blockDim.x / 64;
+  for (long long base = u0 + kFlagsPerWave * wave; base < u1; base += kFlagsPerWave * n_waves) {
+    const long long u = base + lane;
+    uint32_t m = uint32_t(
+        __builtin_amdgcn_ballot_w64(lane < kFlagsPerWave && u < u1 && (flag[u] != 0 || all(u))));
+    while (m) {
+      uint32_t mine = m;  // the grp-th lowest set bit
+      for (int k = 0; k < grp; ++k) mine &= mine - 1;
+      if (mine) f(base + __builtin_ctz(mine), lane % kSumUnit);
+#pragma unroll
+      for (int k = 0; k < 64 / kSumUnit; ++k) m &= m - 1;
+    }
+  }
+}
+static unsigned unit_blocks(long long units) {
+  return unsigned(std::min<long long>((units + 4 * kFlagsPerWave - 1) / (4 * kFlagsPerWave), 32768));
+}
+
+// Also takes each pocket's largest bound over its slots (see mark_poses).
+// fixed: bricks of 64-bit sums per unit (0: one of floats)
+__global__ void __launch_bounds__(256) adj_clear_kernel(const unsigned char* flag, void* sum, int fixed, long long units,
+                                                        unsigned* bound) {
+  if (blockIdx.x == 0 && threadIdx.x < kMaxDiffPockets) {
+    unsigned v = 0;
+    for (int k = 0; k < kBoundSlots; ++k) v = max(v, bound[kMaxDiffPockets + threadIdx.x * kBoundSlots + k]);
+    bound[threadIdx.x] = v;
+  }
+  for_marked_units(flag, 0, units, [](long long) { return false; },
+                   [&](long long u, int at) {
+                     if (!fixed) static_cast<float*>(sum)[u * kSumUnit + at] = 0.f;
+                     for (int k = 0; k < fixed; ++k)
+                       static_cast<unsigned long long*>(sum)[(u * fixed + k) * kSumUnit + at] = 0ull;
+                   });
+}
+
+hipError_t launch_adj_clear(const TermsArgs& a, hipStream_t s) {
+  const long long units = a.unit_off[a.n_pockets];
+  if (units <= 0) return hipSuccess;
+  hipLaunchKernelGGL(adj_clear_kernel, dim3(unit_blocks(units)), dim3(256), 0, s, a.flag, a.sum, a.fixed, units, a.bound);
+  return hipGetLastError();
+}
+
+struct ExpandArgs {
+  TermsArgs t;
+  GridDev grids[kMaxDiffPockets];
+};
+
+// dL/dG[t][k] += the term's sum, or w_k S[t]: 16 lanes per marked unit, which
+// reads its part of the sums once and reads and writes its part of dL/dG
+// once.  Where the fixed-point scale says a bound was not finite, every entry
+// of the pocket becomes NaN.
+template <int K>
+__global__ void __launch_bounds__(256) adj_expand_kernel(ExpandArgs e, long long u0, long long u1) {
+  const TermsArgs& a = e.t;
+  __shared__ double scale[kMaxDiffPockets];
+  if (int(threadIdx.x) < a.n_pockets) scale[threadIdx.x] = a.fixed ? fixed_scale(a, threadIdx.x, K) : 1.0;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
+  auto pocket_of = [&](long long u) {
+    int p = 0;
+    while (u >= a.unit_off[p + 1]) ++p;
+    return p;
+  };
+  for_marked_units(a.flag, u0, u1, [&](long long u) { return scale[pocket_of(u)] == 0.0; },
+                   [&](long long u, int at) {
+                     const int p = pocket_of(u);
+                     const GridDev& g = e.grids[p];
+                     const SumGrid sg = sum_grid(g);
+                     const int ub = int(u - a.unit_off[p]), t = ub / sg.nb, b = ub % sg.nb;
+                     const int ix = b % sg.nbx * kSumX + at % kSumX, iy = b / sg.nbx % sg.nby * kSumY + at / kSumX % kSumY,
+                               iz = b / (sg.nbx * sg.nby) * kSumZ + at / (kSumX * kSumY);
+                     if (ix >= g.dims[0] || iy >= g.dims[1] || iz >= g.dims[2]) return;
+                     const size_t nodes = size_t(g.dims[0]) * g.dims[1] * g.dims[2];
+                     float* dst = a.dLdG[p] + size_t(t) * K * nodes + (size_t(iz) * g.dims[1] + iy) * g.dims[0] + ix;
+                     const double sc = scale[p];
+                     if (sc == 0.0) {
 #pragma unroll
-      for (int k = 0; k < kMaxDiffPockets; ++k) red[k][threadIdx.x] = fmaxf(red[k][threadIdx.x], red[k][threadIdx.x + w]);
-    __syncthreads();
-  }
-  const int pi = threadIdx.x;
-  if (pi < a.n_pockets) {
-    float mw = 0.f;
-    for (int k = 0; k < a.K; ++k) {
-      float v = fabsf(a.w[pi * a.K + k]);
-      if (!(v <= FLT_MAX)) v = INFINITY;
-      mw = fmaxf(mw, v);
-    }
-    const double B = double(a.n_poses) * double(red[pi][0]) * double(mw);
-    double scale = 1.0;
-    if (!(B <= DBL_MAX)) {
-      scale = 0.0;
-    } else if (B > 0.0) {
-      int ex = 0;
-      (void)frexp(B, &ex);
-      scale = ldexp(1.0, 62 - ex);
-    }
-    a.scale[pi] = scale;
-  }
+                       for (int k = 0; k < K; ++k) dst[k * nodes] += __int_as_float(0x7fc00000);
+                     } else if (a.fixed) {
+                       long long v[K];
+#pragma unroll
+                       for (int k = 0; k < K; ++k)
+                         v[k] = static_cast<const long long*>(a.sum)[(u * K + k) * kSumUnit + at];
+                       const double inv = 1.0 / sc;
+#pragma unroll
+                       for (int k = 0; k < K; ++k)
+                         if (v[k] != 0) dst[k * nodes] += float(double(v[k]) * inv);
+                     } else {
+                       const float v = static_cast<const float*>(a.sum)[u * kSumUnit + at];
+                       if (v == 0.f) return;  // no atom reaches the node
+#pragma unroll
+                       for (int k = 0; k < K; ++k) dst[k * nodes] += a.w[p * K + k] * v;
+                     }
+                   });
 }
 
-hipError_t launch_adj_bound(const AdjBoundArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(adj_bound_kernel, dim3(1), dim3(256), 0, s, a);
+hipError_t launch_adj_expand(const TermsArgs& a, const GridDev* grids, int K, long long u0, long long u1, hipStream_t s) {
+  if (u1 <= u0) return hipSuccess;
+  ExpandArgs e;
+  e.t = a;
+  for (int p = 0; p < a.n_pockets; ++p) e.grids[p] = grids[p];
+  if (K == 3)
+    hipLaunchKernelGGL(adj_expand_kernel<3>, dim3(unit_blocks(u1 - u0)), dim3(256), 0, s, e, u0, u1);
+  else
+    hipLaunchKernelGGL(adj_expand_kernel<5>, dim3(unit_blocks(u1 - u0)), dim3(256), 0, s, e, u0, u1);
   return hipGetLastError();
 }
 
-__global__ void adj_finalize_kernel(const unsigned long long* __restrict__ acc, const double* scale, long long n,
-                                    float* __restrict__ dLdG) {
-  const double sc = *scale;
-  const double inv = sc > 0.0 ? 1.0 / sc : 0.0;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const float v = sc > 0.0 ? float(double(static_cast<long long>(acc[i])) * inv) : __int_as_float(0x7fc00000);
-    dLdG[i] += v;
-  }
-}
-
-hipError_t launch_adj_finalize(const unsigned long long* acc, const double* scale, long long n, float* dLdG,
-                               hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const long long blocks = std::min<long long>((n + 255) / 256, 8192);
-  hipLaunchKernelGGL(adj_finalize_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, acc, scale, n, dLdG);
-  return hipGetLastError();
-}
-
-// One workgroup per (pocket, term): thread t sums poses t, t + 256, ... in
+// One workgroup per (pocket, term): thread t sums poses t, t + 1024, ... in
 // order, then a fixed tree over the workgroup.
-__global__ void __launch_bounds__(256) adj_wreduce_kernel(const float* __restrict__ w_pose,
-                                                          const int* __restrict__ w_pocket, long long n_poses,
-                                                          int K, float* dLdw) {
-  __shared__ float red[256];
+__global__ void __launch_bounds__(1024) adj_wreduce_kernel(const float* __restrict__ w_pose,
+                                                           const int* __restrict__ w_pocket, long long n_poses,
+                                                           int K, float* dLdw) {
+  __shared__ float red[1024];
   const int pi = blockIdx.x / K, k = blockIdx.x % K;
   float acc = 0.f;
-  for (long long p = threadIdx.x; p < n_poses; p += 256)
-    if (w_pocket[p] == pi) acc += w_pose[p * K + k];
+#pragma unroll 4
+  for (long long p = threadIdx.x; p < n_poses; p += 1024) {
+    const float v = w_pose[p * K + k];
+    if (w_pocket[p] == pi) acc += v;
+  }
   red[threadIdx.x] = acc;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = 512; w > 0; w >>= 1) {
     if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
@@ -816,21 +980,8 @@ __global__ void __launch_bounds__(256) adj_wreduce_kernel(const float* __restric
 hipError_t launch_adj_wreduce(const float* w_pose, const int* w_pocket, long long n_poses, int n_pockets, int K,
                               float* dLdw, hipStream_t s) {
   if (n_pockets * K <= 0) return hipSuccess;
-  hipLaunchKernelGGL(adj_wreduce_kernel, dim3(unsigned(n_pockets * K)), dim3(256), 0, s, w_pose, w_pocket,
+  hipLaunchKernelGGL(adj_wreduce_kernel, dim3(unsigned(n_pockets * K)), dim3(1024), 0, s, w_pose, w_pocket,
                      n_poses, K, dLdw);
-  return hipGetLastError();
-}
-
-__global__ void zero_u64_kernel(unsigned long long* p, long long n) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    p[i] = 0ull;
-}
-
-hipError_t launch_zero_u64(unsigned long long* p, long long n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const long long blocks = std::min<long long>((n + 255) / 256, 8192);
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, p, n);
   return hipGetLastError();
 }
 
