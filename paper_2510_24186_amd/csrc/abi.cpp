@@ -2138,6 +2138,7 @@ int dock_best_poses(dock_ligands_t L, int32_t n_traj, const float* E_best, const
   int tp = 1;
   while (tp < n_traj) tp <<= 1;
   a.t_pad = tp;
+  a.max_atoms = L->max_atoms;
   if ((size_t(tp) * 8 + 15) / 16 * 16 + size_t(top_n) * kMaxAtoms * 16 > 64 * 1024)
     return fail(DOCK_E_LIMIT, "n_traj * top_n too large for the best-pose LDS budget");
   HIP_TRY(launch_best(a, reinterpret_cast<hipStream_t>(stream)));
@@ -2189,6 +2190,8 @@ static hipError_t rank_passes(const float* scores, int64_t n, int32_t stride, in
   a.n = n;
   a.stride = stride;
   a.k = top_k;
+  a.all = scores;
+  a.stride_all = stride;
   int cur = 0;
   for (;;) {
     const long long blocks = (a.n + kRankBlock - 1) / kRankBlock;

@@ -130,7 +130,7 @@ struct BestArgs {
   float* xyz_out;
   int xyz_stride;
   int* n_out;
-  int t_pad;
+  int t_pad, max_atoms;  // candidates padded to a power of two; largest ligand of the handle
 };
 
 struct MapArgs {
@@ -183,6 +183,8 @@ struct RankArgs {
   long long n;
   int stride;
   int k;
+  const float* all;    // the ligands' scores (ligand i at all[i * stride_all]): what an output value is read from
+  int stride_all;
   float* out_score;
   int* out_idx;
 };

@@ -1272,13 +1272,49 @@ int sample_max_blocks_per_cu(int lpp, int apl, int block, int mode, int local_op
 
 // ================================================================ best poses
 
-__global__ void __launch_bounds__(64) best_kernel(BestArgs a) {
+// Sort key of (value, index): the value's bits mapped to an unsigned key that
+// sorts like the float (-0.0 as +0.0, every NaN after +inf), the index
+// breaking ties.
+DK_INLINE unsigned long long rank_key(float v, int idx) {
+  uint32_t u = __float_as_uint(v);
+  if (v != v) u = 0xffffffffu;
+  else if (u == 0x80000000u) u = 0u;
+  if (u != 0xffffffffu) u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return (static_cast<unsigned long long>(u) << 32) | static_cast<uint32_t>(idx);
+}
+
+// RMSD^2 sum of the lane's atoms against a pose in LDS.
+template <int APL>
+DK_INLINE float sq_diff(const float (&x)[APL][3], const float4* y, int n_atoms, int r) {
+  float acc = 0.f;
+#pragma unroll
+  for (int s = 0; s < APL; ++s) {
+    const int atom = APL * r + s;
+    if (atom < n_atoms) {
+      const float4 v = y[atom];
+      const float dx = x[s][0] - v.x, dy = x[s][1] - v.y, dz = x[s][2] - v.z;
+      acc += dx * dx + dy * dy + dz * dz;
+    }
+  }
+  return acc;
+}
+
+// A workgroup per ligand: the candidates' keys sorted in LDS, then W at a
+// time (one per wave) placed, compared with the kept poses and, in order,
+// with those of the same turn that were kept.  Bound by the latency of a
+// turn's placement and comparisons, which four waves share where ligands are
+// few (one ligand with 1,024 candidates: 134 -> 27 us, the sort included);
+// LDS is sized by the handle's largest ligand (4,096 ligands x 64 candidates:
+// 157 -> 122 us).
+template <int W>
+__global__ void __launch_bounds__(64 * W) best_kernel(BestArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int LPP = 64, APL = 2;
-  const int lig = blockIdx.x, r = threadIdx.x;
-  float* kE = reinterpret_cast<float*>(smem);
-  int* kI = reinterpret_cast<int*>(kE + a.t_pad);
-  float4* kept = reinterpret_cast<float4*>(smem + (size_t(a.t_pad) * 8 + 15) / 16 * 16);  // [top_n][kMaxAtoms]
+  __shared__ int s_kept[W];
+  const int lig = blockIdx.x, tid = threadIdx.x, r = tid & 63, wv = tid >> 6;
+  unsigned long long* key = reinterpret_cast<unsigned long long*>(smem);
+  float4* kept = reinterpret_cast<float4*>(smem + (size_t(a.t_pad) * 8 + 15) / 16 * 16);  // [top_n][max_atoms]
+  float4* cand = kept + size_t(a.top_n) * a.max_atoms;                                     // [W][max_atoms], W > 1
   const LigDev lg = a.L.ligs[lig];
   PocketDev none;
   none.preset = DOCK_PRESET_TRIDS;
@@ -1286,61 +1322,92 @@ __global__ void __launch_bounds__(64) best_kernel(BestArgs a) {
   LaneLig<APL> L;
   load_lane_lig<LPP, APL>(L, lg, a.L.ligs + lig, a.L.atoms, a.L.frags, a.L.tors, none, r);
   const int T = a.n_traj;
-  for (int i = r; i < a.t_pad; i += 64) {
+  const unsigned long long inf_key = rank_key(INFINITY, 0);
+  for (int i = tid; i < a.t_pad; i += 64 * W) {
     float e = i < T ? a.E_best[size_t(lig) * T + i] : INFINITY;
     if (!(e < INFINITY)) e = INFINITY;  // NaN and +inf rank last
-    kE[i] = e;
-    kI[i] = i < T ? i : 0x7fffffff;
+    key[i] = rank_key(e, i < T ? i : 0x7fffffff);
   }
-  wave_sync();
+  auto sync = [] {
+    if (W > 1)
+      __syncthreads();
+    else
+      wave_sync();
+  };
+  sync();
   for (int k = 2; k <= a.t_pad; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = r; i < a.t_pad; i += 64) {
-        const int l = i ^ j;
-        if (l > i) {
-          const float ei = kE[i], el = kE[l];
-          const int ii = kI[i], il = kI[l];
-          const bool gt = ei > el || (ei == el && ii > il);
-          const bool up = (i & k) == 0;
-          if (gt == up) {
-            kE[i] = el; kE[l] = ei;
-            kI[i] = il; kI[l] = ii;
-          }
+      for (int p = tid; p < a.t_pad / 2; p += 64 * W) {
+        const int lo = 2 * p - (p & (j - 1)), hi = lo + j;
+        const unsigned long long kl = key[lo], kh = key[hi];
+        if ((kl > kh) == ((lo & k) == 0)) {
+          key[lo] = kh;
+          key[hi] = kl;
         }
       }
-      wave_sync();
+      sync();
     }
   }
   int n_kept = 0;
   const float inv_n = 1.0f / float(lg.n_atoms);
-  for (int c = 0; c < T && n_kept < a.top_n; ++c) {
-    const float E = kE[c];
-    if (!(E < INFINITY)) break;
-    const int t = kI[c];
-    const float q = r < lg.n_dof ? a.q_best[(size_t(lig) * T + t) * a.q_stride + r] : 0.f;
+  auto near = [&](float acc) { return sqrtf(group_sum<64>(acc) * inv_n) < a.rmsd_cut; };
+  // this wave's candidate of the next turn: read ahead of the comparisons
+  auto cand_of = [&](int c) { return c < T && key[c] < inf_key ? int(uint32_t(key[c])) : -1; };
+  auto q_of = [&](int t) {
+    return t >= 0 && r < lg.n_dof ? a.q_best[(size_t(lig) * T + t) * a.q_stride + r] : 0.f;
+  };
+  int t = cand_of(wv);
+  float q = q_of(t);
+  for (int c = 0; c < T && n_kept < a.top_n && key[c] < inf_key; c += W) {
+    const int t_next = cand_of(c + W + wv);
+    const float q_next = q_of(t_next);
     float x[APL][3];
     fk_place_shfl<LPP, APL>(L, q, r, x);
-    bool dup = false;
-    for (int k = 0; k < n_kept && !dup; ++k) {
-      float acc = 0.f;
+    bool dup = t < 0;
+    for (int k = 0; k < n_kept && !dup; k += 4) {
+      // four at a time: their sums and square roots overlap
+      float acc[4];
 #pragma unroll
-      for (int s = 0; s < APL; ++s) {
-        const int atom = APL * r + s;
-        if (atom < lg.n_atoms) {
-          const float4 y = kept[k * kMaxAtoms + atom];
-          const float dx = x[s][0] - y.x, dy = x[s][1] - y.y, dz = x[s][2] - y.z;
-          acc += dx * dx + dy * dy + dz * dz;
-        }
-      }
-      dup = sqrtf(group_sum<64>(acc) * inv_n) < a.rmsd_cut;
+      for (int m = 0; m < 4; ++m) acc[m] = sq_diff<APL>(x, kept + size_t(min(k + m, n_kept - 1)) * a.max_atoms, lg.n_atoms, r);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) dup |= near(acc[m]);
     }
-    if (!dup) {
-      const size_t o = size_t(lig) * a.top_n + n_kept;
+    if (W > 1) {
+#pragma unroll
+      for (int s = 0; s < APL; ++s)
+        if (APL * r + s < lg.n_atoms) cand[wv * a.max_atoms + APL * r + s] = make_float4(x[s][0], x[s][1], x[s][2], 0.f);
+      if (r == 0) s_kept[wv] = !dup;
+      __syncthreads();
+      // in order: a candidate is compared with those of this turn that stay
+      for (int m = 0; m + 1 < W; ++m) {
+        const bool stays = s_kept[m];
+        if (stays && wv > m && !dup) {
+          dup = near(sq_diff<APL>(x, cand + m * a.max_atoms, lg.n_atoms, r));
+          if (dup && r == 0) s_kept[wv] = 0;
+        }
+        __syncthreads();
+      }
+    }
+    // slots in order, up to top_n
+    int slot = n_kept;
+    if (W > 1) {
+      int total = n_kept;
+#pragma unroll
+      for (int m = 0; m < W; ++m) {
+        slot += m < wv && s_kept[m];
+        total += s_kept[m];
+      }
+      n_kept = min(total, a.top_n);
+    } else if (!dup) {
+      ++n_kept;
+    }
+    if (!dup && slot < a.top_n) {
+      const size_t o = size_t(lig) * a.top_n + slot;
 #pragma unroll
       for (int s = 0; s < APL; ++s) {
         const int atom = APL * r + s;
         if (atom < lg.n_atoms) {
-          kept[n_kept * kMaxAtoms + atom] = make_float4(x[s][0], x[s][1], x[s][2], 0.f);
+          kept[size_t(slot) * a.max_atoms + atom] = make_float4(x[s][0], x[s][1], x[s][2], 0.f);
           if (a.xyz_out) {
             float* dst = a.xyz_out + o * a.xyz_stride + 3 * L.aorig[s];
             dst[0] = x[s][0];
@@ -1350,15 +1417,18 @@ __global__ void __launch_bounds__(64) best_kernel(BestArgs a) {
         }
       }
       if (r == 0) {
+        const float E = a.E_best[size_t(lig) * T + t];
         if (a.E_out) a.E_out[o] = E;
         if (a.E_screen) a.E_screen[o] = E / (1.0f + a.w_tor * float(lg.n_tors));
         if (a.idx_out) a.idx_out[o] = t;
       }
       if (a.q_out && r < a.q_stride) a.q_out[o * a.q_stride + r] = r < lg.n_dof ? q : 0.f;
-      ++n_kept;
     }
-    wave_sync();
+    sync();
+    t = t_next;
+    q = q_next;
   }
+  if (wv > 0) return;
   for (int k = n_kept; k < a.top_n; ++k) {
     const size_t o = size_t(lig) * a.top_n + k;
     if (r == 0) {
@@ -1372,75 +1442,102 @@ __global__ void __launch_bounds__(64) best_kernel(BestArgs a) {
 }
 
 hipError_t launch_best(const BestArgs& a, hipStream_t s) {
-  const size_t lds = (size_t(a.t_pad) * 8 + 15) / 16 * 16 + size_t(a.top_n) * kMaxAtoms * 16;
   if (a.n_ligands <= 0) return hipSuccess;
-  hipLaunchKernelGGL(best_kernel, dim3(a.n_ligands), dim3(64), lds, s, a);
+  auto lds = [&](int waves) {
+    return (size_t(a.t_pad) * 8 + 15) / 16 * 16 + size_t(a.top_n + (waves > 1 ? waves : 0)) * a.max_atoms * 16;
+  };
+  // four waves per ligand until the ligands alone fill the chip several times
+  // (x 64 candidates: 4,096 ligands 122 us with four, 147 with one; 16,384 398
+  // and 335), where the LDS allows
+  if (a.n_ligands <= 4096 && lds(4) <= 64 * 1024)
+    hipLaunchKernelGGL(best_kernel<4>, dim3(a.n_ligands), dim3(256), lds(4), s, a);
+  else
+    hipLaunchKernelGGL(best_kernel<1>, dim3(a.n_ligands), dim3(64), lds(1), s, a);
   return hipGetLastError();
 }
 
 // ================================================================ screening rank
 
-// Total order on (score, index): the score's bits mapped to an unsigned key
-// that sorts like the float (-0.0 as +0.0, every NaN after +inf), the
-// ligand index breaking ties.
-DK_INLINE unsigned long long rank_key(float v, int idx) {
-  uint32_t u = __float_as_uint(v);
-  if (v != v) u = 0xffffffffu;
-  else if (u == 0x80000000u) u = 0u;
-  if (u != 0xffffffffu) u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return (static_cast<unsigned long long>(u) << 32) | static_cast<uint32_t>(idx);
-}
-
-__global__ void __launch_bounds__(256) rank_kernel(RankArgs a) {
+// A workgroup sorts a block of 2,048 keys, two per thread (elements 2 t and
+// 2 t + 1).  Exchanges within a thread's pair are free and those within a
+// wave are shuffles, so only distances of 128 and more, 10 of the 66 steps, go
+// through LDS with a barrier (2,048 scores: 46 us with every step in LDS on 256
+// threads and the values carried along, 15 so).
+__global__ void __launch_bounds__(kRankBlock / 2) rank_kernel(RankArgs a) {
   __shared__ unsigned long long key[kRankBlock];
-  __shared__ float val[kRankBlock];
   const long long base = (long long)blockIdx.x * kRankBlock;
-  for (int t = threadIdx.x; t < kRankBlock; t += 256) {
-    const long long e = base + t;
+  const int tid = threadIdx.x;
+  unsigned long long k2[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const long long e = base + 2 * tid + h;
+    k2[h] = ~0ull;
     if (e < a.n) {
       const float v = a.idx ? a.score[e] : a.score[e * a.stride];
       const int id = a.idx ? a.idx[e] : int(e);
       // an empty slot of an earlier pass (index -1) stays empty
-      key[t] = id < 0 ? ~0ull : rank_key(v, id);
-      val[t] = v;
-    } else {
-      key[t] = ~0ull;
-      val[t] = __int_as_float(0x7f800000);
+      if (id >= 0) k2[h] = rank_key(v, id);
     }
   }
-  __syncthreads();
-  // bitonic sort of kRankBlock keys (values follow their key)
+  auto order = [](unsigned long long& lo, unsigned long long& hi, bool up) {
+    if ((lo > hi) == up) {
+      const unsigned long long t = lo;
+      lo = hi;
+      hi = t;
+    }
+  };
   for (int size = 2; size <= kRankBlock; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = threadIdx.x; t < kRankBlock / 2; t += 256) {
-        const int lo = 2 * t - (t & (stride - 1));
-        const int hi = lo + stride;
-        const bool up = (lo & size) == 0;
-        const unsigned long long kl = key[lo], kh = key[hi];
-        if ((kl > kh) == up) {
-          key[lo] = kh;
-          key[hi] = kl;
-          const float vl = val[lo];
-          val[lo] = val[hi];
-          val[hi] = vl;
-        }
-      }
+    const bool up = ((2 * tid) & size) == 0;
+    for (int stride = size >> 1; stride > 64; stride >>= 1) {
+      // through LDS: thread t takes the pair (lo, lo + stride)
+      key[2 * tid] = k2[0];
+      key[2 * tid + 1] = k2[1];
+      __syncthreads();
+      const int lo = 2 * tid - (tid & (stride - 1));
+      unsigned long long x = key[lo], y = key[lo + stride];
+      order(x, y, (lo & size) == 0);
+      key[lo] = x;
+      key[lo + stride] = y;
+      __syncthreads();
+      k2[0] = key[2 * tid];
+      k2[1] = key[2 * tid + 1];
       __syncthreads();
     }
+    for (int stride = size >> 1 > 64 ? 64 : size >> 1; stride > 1; stride >>= 1) {
+      // partner thread t ^ (stride / 2) holds elements 2 t + h +- stride
+      const bool low = (tid & (stride / 2)) == 0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const unsigned long long o = __shfl_xor(k2[h], stride / 2);
+        const bool take = (k2[h] > o) == (low == up);
+        if (take && k2[h] != o) k2[h] = o;
+      }
+    }
+    order(k2[0], k2[1], up);
   }
+  // values from the ligands' scores, read before any is written (a caller may
+  // rank in place)
   const int keep = a.k < kRankBlock ? a.k : kRankBlock;
-  for (int t = threadIdx.x; t < keep; t += 256) {
-    const unsigned long long kv = key[t];
-    const bool none = kv == ~0ull;
-    a.out_score[(long long)blockIdx.x * keep + t] = none ? __int_as_float(0x7f800000) : val[t];
-    a.out_idx[(long long)blockIdx.x * keep + t] = none ? -1 : int(uint32_t(kv));
+  float v2[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    v2[h] = __int_as_float(0x7f800000);
+    if (2 * tid + h < keep && k2[h] != ~0ull) v2[h] = a.all[(long long)(uint32_t(k2[h])) * a.stride_all];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int t = 2 * tid + h;
+    if (t >= keep) continue;
+    a.out_score[(long long)blockIdx.x * keep + t] = v2[h];
+    a.out_idx[(long long)blockIdx.x * keep + t] = k2[h] == ~0ull ? -1 : int(uint32_t(k2[h]));
   }
 }
 
 hipError_t launch_rank(const RankArgs& a, hipStream_t s) {
   const long long nb = (a.n + kRankBlock - 1) / kRankBlock;
   const unsigned blocks = unsigned(nb > 0 ? nb : 1);
-  hipLaunchKernelGGL(rank_kernel, dim3(blocks), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(rank_kernel, dim3(blocks), dim3(kRankBlock / 2), 0, s, a);
   return hipGetLastError();
 }
 
