@@ -1629,13 +1629,22 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   // trajectory count only, so every form of the run evaluates alike.
   const bool one_per_lane = (ov && ov->one_per_lane >= 0) ? ov->one_per_lane != 0
                                                             : run_one_per_lane(L, r->T, n_cu, ov ? ov->subset : nullptr);
+  // A run of no more trajectories than the device has SIMDs takes workgroups
+  // of one wavefront: its steps are a serial chain, and the waves of a larger
+  // workgroup wait for each other's LDS accesses on one CU while others idle
+  // (64 trajectories of a 24-atom ligand, 100 steps: 3.38 ms with workgroups
+  // of 256 threads, 3.19 with 64; at the line, 1,024 of a 35-atom ligand in
+  // 64-lane groups, 0.574 and 0.572 ms for 10 steps).
+  const bool spread = (long long)r->n_lig * r->T <= 4LL * n_cu;
   for (int l = 0; l < r->n_lig; ++l) {
     LaneCfg c = lane_cfg(L->h_ligs[l], p->lanes_per_pose, one_per_lane);
     int block = 256;
+    bool one_wave = spread;
     if (ov && ov->lpp) {
       if (c.lpp == ov->nat_lpp && c.apl == ov->nat_apl) {
         c.lpp = ov->lpp;
         block = ov->block;
+        one_wave = false;
       }
     } else if (p->lanes_per_pose == 0) {
       std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1643,6 +1652,7 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
       if (t != g_tune.end()) {
         c.lpp = t->second.lpp;
         block = t->second.block;
+        one_wave = false;
       }
     }
     // ligands whose staged pair records lower the blocks per CU go to a
@@ -1651,6 +1661,9 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
     const LigDev& gl0 = L->h_ligs[l];
     const int stage = c.apl == 1 ? gl0.alt.n_stage : gl0.n_stage;
     const size_t lds_l = sample_lds_bytes(c.lpp, c.apl, block, stage);
+    // (runs of one-wave workgroups keep the classes and the LDS limit of
+    // 256 threads: as many launches, the same ligands refused)
+    if (one_wave && lds_l > 64 * 1024) return bail(DOCK_E_LIMIT, "pair list too long for the LDS budget");
     int per_cu = 0;
     if (p->form == DOCK_FORM_BATCHED && lds_l <= 64 * 1024) {
       const auto ok = std::make_tuple(c.lpp, c.apl, block, int((lds_l + 255) / 256));
@@ -1660,6 +1673,7 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
                                                          (lds_l + 255) / 256 * 256)).first;
       per_cu = oi->second;
     }
+    if (one_wave) block = 64;
     auto key = std::make_tuple(c.lpp, c.apl, block, per_cu);
     auto it = bidx.find(key);
     if (it == bidx.end()) {
