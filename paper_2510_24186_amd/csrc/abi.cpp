@@ -2175,17 +2175,17 @@ int dock_pocket_map_adjoint(dock_pocket_t p, const float* dLdG, float* dLdxyz, d
   a.lam = dLdG;
   a.dLdxyz = dLdxyz;
   a.dLdtheta = dLdtheta;
-  // brick flags in stream-ordered scratch; a call under capture (which would
+  // node masks in stream-ordered scratch; a call under capture (which would
   // record the allocation) or without memory for it does without
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (p->n_rec > 0 && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-      hipMallocAsync(reinterpret_cast<void**>(&a.flag), size_t(map_adjoint_bricks(a.grid)), s) != hipSuccess) {
+      hipMallocAsync(reinterpret_cast<void**>(&a.mask), size_t(map_adjoint_bricks(a.grid)) * 8, s) != hipSuccess) {
     (void)hipGetLastError();
-    a.flag = nullptr;
+    a.mask = nullptr;
   }
   const hipError_t e = launch_map_adjoint(a, s);
-  if (a.flag) (void)hipFreeAsync(a.flag, s);
+  if (a.mask) (void)hipFreeAsync(a.mask, s);
   HIP_TRY(e);
   return DOCK_OK;
 } catch (...) {

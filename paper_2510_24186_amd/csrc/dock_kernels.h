@@ -155,8 +155,8 @@ struct MapAdjArgs {
   const float* lam;    // dL/dG [8][3][nodes]
   float* dLdxyz;       // [n_rec * 3], +=
   double* dLdtheta;    // [kMapTheta], +=
-  unsigned char* flag; // scratch, one byte per brick of nodes (map_adjoint_bricks), or null:
-                       // every brick counts as holding a nonzero lambda
+  unsigned long long* mask;  // scratch, a bit per node in words of one brick (map_adjoint_bricks), or
+                             // null: every node counts as holding a nonzero lambda
 };
 long long map_adjoint_bricks(const GridDev& g);
 hipError_t launch_map_adjoint(const MapAdjArgs& a, hipStream_t s);

@@ -219,10 +219,11 @@ hipError_t launch_map_build(const MapArgs& a, hipStream_t s) {
 // Bricks of 8 x 4 x 2 nodes, one per wavefront.
 constexpr int kAdjX = 8, kAdjY = 4, kAdjZ = 2;
 
-// flag[b] = 1 where some lambda of brick b is not zero (one wave per brick).
-__global__ void __launch_bounds__(256) map_adjoint_flags_kernel(const float* __restrict__ lam, int nx, int ny, int nz,
-                                                                int nbx, int nby, long long n_bricks,
-                                                                unsigned char* __restrict__ flag) {
+// mask[b]: the nodes of brick b, bit x + 8 y + 32 z, where some lambda is not
+// zero (one wave per brick).
+__global__ void __launch_bounds__(256) map_adjoint_mask_kernel(const float* __restrict__ lam, int nx, int ny, int nz,
+                                                               int nbx, int nby, long long n_bricks,
+                                                               unsigned long long* __restrict__ mask) {
   const long long b = (long long)blockIdx.x * 4 + threadIdx.x / 64;
   if (b >= n_bricks) return;
   const int lane = threadIdx.x & 63;
@@ -234,8 +235,8 @@ __global__ void __launch_bounds__(256) map_adjoint_flags_kernel(const float* __r
 #pragma unroll
     for (int q = 0; q < 3 * kTypes; ++q) any |= lam[q * nodes + node] != 0.f;
   }
-  if (__builtin_amdgcn_ballot_w64(any) && lane == 0) flag[b] = 1;
-  else if (lane == 0) flag[b] = 0;
+  const unsigned long long m = __builtin_amdgcn_ballot_w64(any);
+  if (lane == 0) mask[b] = m;
 }
 
 DK_INLINE double wave_sum(double v) {
@@ -246,18 +247,21 @@ DK_INLINE double wave_sum(double v) {
 
 // One workgroup per receptor atom over the bricks around it: a wave tests 64
 // bricks at a time (inside the cutoff at their nearest point, and with a
-// nonzero lambda where flags are given: the lambda of a set of docked poses
-// is zero in most of a pocket), then takes the hits one by one, a node per
-// lane (the same FP32 cutoff decisions as map_kernel).  The chain rule in
-// FP64: per node one exponential for each of the three radius classes of the
-// ligand types, the short-range terms where the node is near.  Bound by
+// nonzero lambda where masks are given: the lambda of a set of docked poses
+// is zero in most of a pocket), then the nodes of each hit (the same FP32
+// cutoff decisions as map_kernel), and queues the numbers of those that count
+// in LDS; 64 queued nodes are taken at a time, one per lane.  The chain rule
+// in FP64: per node one exponential for each of the three radius classes of
+// the ligand types, the short-range terms where the node is near.  Bound by
 // those exponentials (256 poses' lambda, 2,000 atoms, 64^3 nodes: 2.69 ms
-// before, with every node of the box and every type's exponential, now under
-// 0.4 ms).  dL/dr is written once per atom in a fixed order (no
-// atomics); dL/dtheta takes 13 atomic adds per atom.
+// with every node of the box and every type's exponential, 0.48 ms with every
+// node of a brick that holds a nonzero lambda, of which three in ten counted,
+// now 0.28 ms).  dL/dr is written once per atom in a fixed order (no atomics);
+// dL/dtheta takes 13 atomic adds per atom.
 __global__ void __launch_bounds__(256) map_adjoint_kernel(MapAdjArgs a) {
   __shared__ double red[4][3 + kMapTheta];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ uint32_t queue[4][128];  // per wave, a ring: ix | iy << 10 | iz << 20 (dims <= 1024)
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = blockIdx.x;
   const float4 ri = a.rec[i];
   const int u = __builtin_amdgcn_readfirstlane(__float_as_int(ri.w)) & 0xff;
@@ -295,11 +299,10 @@ __global__ void __launch_bounds__(256) map_adjoint_kernel(MapAdjArgs a) {
   // dL/dr; per ligand type sum of lambda g x / sigma^2 (E_long) and of
   // lambda / d_clash (pairs without a hydrogen bond); the other constants
   double dr[3] = {}, rl[kTypes] = {}, rc[kTypes] = {}, sig_l = 0.0, mu_h = 0.0, sig_h = 0.0, dc_h = 0.0;
-  auto take_node = [&](int ix, int iy, int iz) {
-    if (ix >= nx || iy >= ny || iz >= nz) return;
+  auto take_node = [&](uint32_t code) {
+    const int ix = code & 1023u, iy = (code >> 10) & 1023u, iz = code >> 20;
     const float px = coord(0, ix), py = coord(1, iy), pz = coord(2, iz);
     const float d2 = d2_rounded(px - ri.x, py - ri.y, pz - ri.z);
-    if (!(d2 < 100.0f)) return;
     const double ex = double(ri.x) - double(px), ey = double(ri.y) - double(py), ez = double(ri.z) - double(pz);
     const double d = sqrt(ex * ex + ey * ey + ez * ez);
     const float* lt = a.lam + ((long long)iz * ny + iy) * nx + ix;
@@ -357,9 +360,10 @@ __global__ void __launch_bounds__(256) map_adjoint_kernel(MapAdjArgs a) {
       dr[2] += f * ez;
     }
   };
+  int head = 0, queued = 0;  // of the wave's ring
   for (long long base = 64 * wv; base < nb; base += 256) {
     const long long q = base + lane;
-    bool hit = false;
+    unsigned long long nz_mask = 0;  // nodes of this lane's brick to test
     int bx = 0, by = 0, bz = 0;
     if (q < nb) {
       bx = lo[0] + int(q % cnt[0]);
@@ -370,18 +374,36 @@ __global__ void __launch_bounds__(256) map_adjoint_kernel(MapAdjArgs a) {
         const int k0 = b * bs[axis], k1 = min(k0 + bs[axis], n) - 1;
         return fmaxf(fmaxf(coord(axis, k0) - p, p - coord(axis, k1)), 0.f);
       };
-      hit = d2_rounded(gap(0, bx, ri.x, nx), gap(1, by, ri.y, ny), gap(2, bz, ri.z, nz)) < 100.0f;
-      if (hit && a.flag) hit = a.flag[((long long)bz * nby + by) * nbx + bx] != 0;
+      if (d2_rounded(gap(0, bx, ri.x, nx), gap(1, by, ri.y, ny), gap(2, bz, ri.z, nz)) < 100.0f)
+        nz_mask = a.mask ? a.mask[((long long)bz * nby + by) * nbx + bx] : ~0ull;
     }
-    unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    unsigned long long m = __builtin_amdgcn_ballot_w64(nz_mask != 0);
     while (m) {
       const int l = __builtin_ctzll(m);
       m &= m - 1;
-      take_node(__builtin_amdgcn_readlane(bx, l) * kAdjX + lane % kAdjX,
-                __builtin_amdgcn_readlane(by, l) * kAdjY + lane / kAdjX % kAdjY,
-                __builtin_amdgcn_readlane(bz, l) * kAdjZ + lane / (kAdjX * kAdjY));
+      const unsigned long long nm = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(int(nz_mask >> 32), l) << 32 |
+                                    (uint32_t)__builtin_amdgcn_readlane(int(nz_mask), l);
+      const int ix = __builtin_amdgcn_readlane(bx, l) * kAdjX + lane % kAdjX,
+                iy = __builtin_amdgcn_readlane(by, l) * kAdjY + lane / kAdjX % kAdjY,
+                iz = __builtin_amdgcn_readlane(bz, l) * kAdjZ + lane / (kAdjX * kAdjY);
+      const bool in = (nm >> lane & 1) && ix < nx && iy < ny && iz < nz &&
+                      d2_rounded(coord(0, ix) - ri.x, coord(1, iy) - ri.y, coord(2, iz) - ri.z) < 100.0f;
+      const unsigned long long im = __builtin_amdgcn_ballot_w64(in);
+      if (in)
+        queue[wv][(head + queued + __popcll(im & ((1ull << lane) - 1))) & 127] =
+            uint32_t(ix) | uint32_t(iy) << 10 | uint32_t(iz) << 20;
+      queued += __popcll(im);
+      if (queued >= 64) {
+        wave_sync();
+        take_node(queue[wv][(head + lane) & 127]);
+        head = (head + 64) & 127;
+        queued -= 64;
+        wave_sync();
+      }
     }
   }
+  wave_sync();
+  if (lane < queued) take_node(queue[wv][(head + lane) & 127]);
   // sums over the workgroup; theta = (mu_long, sigma_long, mu_hb, sigma_hb,
   // d_clash_hb, R_0 .. R_7), both types of a pair taking its radius terms
   double all[3 + kMapTheta];
@@ -424,11 +446,11 @@ long long map_adjoint_bricks(const GridDev& g) {
 
 hipError_t launch_map_adjoint(const MapAdjArgs& a, hipStream_t s) {
   if (a.n_rec <= 0) return hipSuccess;
-  if (a.flag) {
+  if (a.mask) {
     const long long n = map_adjoint_bricks(a.grid);
     const int nbx = (a.grid.dims[0] + kAdjX - 1) / kAdjX, nby = (a.grid.dims[1] + kAdjY - 1) / kAdjY;
-    hipLaunchKernelGGL(map_adjoint_flags_kernel, dim3(unsigned((n + 3) / 4)), dim3(256), 0, s, a.lam, a.grid.dims[0],
-                       a.grid.dims[1], a.grid.dims[2], nbx, nby, n, a.flag);
+    hipLaunchKernelGGL(map_adjoint_mask_kernel, dim3(unsigned((n + 3) / 4)), dim3(256), 0, s, a.lam, a.grid.dims[0],
+                       a.grid.dims[1], a.grid.dims[2], nbx, nby, n, a.mask);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

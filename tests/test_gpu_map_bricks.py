@@ -70,3 +70,31 @@ def test_map_adjoint_of_sparse_lambda(dims, n, radius, some):
     ref_x, ref_t = MA.map_adjoint(pk, lam.astype(np.float64))
     assert np.abs(dx.cpu().numpy() - ref_x).max() <= 1e-6 * max(1.0, np.abs(ref_x).max())
     assert np.all(np.abs(dth.cpu().numpy() - ref_t) <= 1e-9 * np.maximum(1.0, np.abs(ref_t).max()))
+
+
+def test_map_adjoint_under_capture():
+    """A captured call goes without the node masks (their scratch cannot be
+    allocated there): the same sums in another order."""
+    D = G.lib()
+    G.say("map adjoint bricks, captured")
+    dims, n = (17, 9, 6), 300
+    pk = _pocket(n, dims, 12.0, seed=3)
+    p = G.load_pocket(pk)
+    lam = np.random.default_rng(4).normal(size=(8, 3) + dims[::-1]).astype(np.float32)
+    lam[..., ::3] = 0.0
+    lam = torch.tensor(lam, device="cuda")
+    new = lambda: (torch.zeros((n, 3), device="cuda"), torch.zeros(13, dtype=torch.float64, device="cuda"))
+    ref_x, ref_t = new()
+    D.dock_pocket_map_adjoint(p, lam, ref_x, ref_t)
+    dx, dth = new()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        D.dock_pocket_map_adjoint(p, lam, dx, dth)
+    for _ in range(3):
+        dx.zero_()
+        dth.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert (dx - ref_x).abs().max() <= 1e-6 * max(1.0, float(ref_x.abs().max()))
+        assert (dth - ref_t).abs().max() <= 1e-9 * max(1.0, float(ref_t.abs().max()))
