@@ -50,7 +50,10 @@ PAPER_MEM_MB = 380.0   # Table 5: GPU memory per docking, RTX A6000 (context onl
 def flops_per_eval(n_atoms, n_pairs, n_tors):
     """Algorithmic FP32 operations of one score + gradient evaluation: per atom
     ~15 for the placement, ~65 for the trilinear value and gradient, ~25 for
-    the chain rule; ~50 per intra-ligand pair; ~60 per torsion."""
+    the chain rule; ~50 per intra-ligand pair; ~60 per torsion.  A sampler
+    evaluation that needs only the energy or only the gradient (an unlogged
+    run's) counts as one such evaluation too: this is the algorithm's count,
+    not the executed one."""
     return 105.0 * n_atoms + 50.0 * n_pairs + 60.0 * n_tors
 
 

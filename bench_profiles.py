@@ -96,7 +96,7 @@ def trace_summaries(runs, out):
     dom_trace = [d for n, g, wg, d, lds, scr, st in rows if key in short(n) and g == grid_threads][-1] / 1e6
     lines += ["", "The first six dispatches draw and score the initial poses; the next six are the MC-step "
               "launches of", "the six buckets, concurrent within each occupancy class (three blocks per CU, "
-              "then two).  The dominant", "launch (most algorithmic work) is", "`%s, 0>` with grid %d threads: %.3f ms here;" % (key, grid_threads, dom_trace),
+              "then two).  The dominant", "launch (most algorithmic work) is", "`%s, 0, false>` with grid %d threads: %.3f ms here;" % (key, grid_threads, dom_trace),
               "bench.py measured the same launch with HIP events on its stream as %.3f ms (`roofline.launch_ms`)."
               % dom["launch_ms"], "",
               "Same run, bench line: value %.1f M evals/s, dominant launch %.3f TFLOP/s = %.4f of 157.3." % (
@@ -106,10 +106,11 @@ def trace_summaries(runs, out):
     terms = [(short(n), g, dur / 1e6) for n, g, wg, dur, lds, scr, st in rows if "terms_kernel" in n or "adj_" in n]
     tl = ["# Kernel trace: the differentiable form (terms_kernel and the deterministic adjoint's helpers)", "",
           "From the same rocprofv3 run as sample_kernel_mixed16_trace.md:", "", "    " + CMD_TRACE, "",
-          "* `terms_kernel<64, 2, 3, false>`: the adjoint over the 65,536 best poses of the mixed-pocket step "
-          "(TRIDS,", "  16 pockets, deterministic: 64-bit fixed-point dL/dG).",
-          "* `terms_kernel<64, 1, 5, false>`: the differentiation workload (2,048 poses, Vina-form terms, "
-          "64^3 x 8 x 5", "  maps): forward, adjoint with float atomics, adjoint deterministic, twice.", "",
+          "* `terms_kernel<3, false, true>`: the adjoint over the 65,536 best poses of the mixed-pocket step "
+          "(TRIDS,", "  16 pockets, deterministic: 64-bit fixed-point dL/dG), between `adj_mark_kernel` and "
+          "`adj_expand_kernel`.",
+          "* `terms_kernel<5, false, false>` and `<5, false, true>`: the differentiation workload (2,048 poses, "
+          "Vina-form", "  terms, 64^3 x 8 x 5 maps): forward, adjoint, adjoint deterministic, twice.", "",
           "| Kernel | Grid (threads) | Duration ms |", "|---|---|---|"]
     for k, g, d in terms:
         tl.append("| `%s` | %d | %.3f |" % (k, g, d))
