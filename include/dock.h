@@ -238,7 +238,7 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
  * All pockets of a call share one preset; n_pockets <= 16.
  *   deterministic  0: dL/dG by float atomics (summation order, and so the last
  *                     bits, vary from call to call; so does dL/dw in calls of
- *                     fewer than 256 poses);
+ *                     fewer than 768 poses);
  *                  1: bitwise repeatable.  dL/dG is summed as 64-bit
  *                     integers: every corner contribution is rounded once to
  *                     a multiple of 2^(e - 62), where 2^e bounds any node's
@@ -248,7 +248,7 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
  *                     poses in a fixed order.  Non-finite dLdE or w make
  *                     that pocket's dL/dG NaN.
  *   Scratch is allocated and released on the stream: 8 bytes per dL/dG entry
- *   (deterministic) or 4 bytes per node and type (otherwise, from 256 poses
+ *   (deterministic) or 4 bytes per node and type (otherwise, from 768 poses
  *   on and outside stream capture), of which only the surroundings of the
  *   poses' atoms are touched, and 4 (K + 1) bytes per pose.
  * Ligand-internal pair forces are summed in FP64 in a fixed order, or as

@@ -79,6 +79,53 @@ static void dev_free(T*& p) {
   p = nullptr;
 }
 
+// ---------------------------------------------------------------- scratch
+
+// Stream-ordered scratch of the adjoints, from a pool of the library's own
+// per device.  The device's default pool returns its memory at every
+// synchronisation, and a call after one then mapped its scratch anew (a
+// deterministic adjoint of 256 poses: 423 us after a synchronisation, 95
+// back to back).  This one keeps up to kScratchKeep between calls and gives
+// it back when a pocket or ligand handle is freed.
+constexpr uint64_t kScratchKeep = 128ull << 20;
+static std::mutex g_scratch_mu;
+static std::map<int, hipMemPool_t> g_scratch;
+
+static hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = 0;
+  hipMemPool_t pool = nullptr;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+      hipGetDevice(&dev) == hipSuccess) {
+    std::lock_guard<std::mutex> lk(g_scratch_mu);
+    auto it = g_scratch.find(dev);
+    if (it == g_scratch.end()) {
+      hipMemPoolProps props{};
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = dev;
+      uint64_t keep = kScratchKeep;
+      if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
+        pool = nullptr;
+      } else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+        (void)hipMemPoolDestroy(pool);
+        pool = nullptr;
+      }
+      (void)hipGetLastError();
+      it = g_scratch.emplace(dev, pool).first;
+    }
+    pool = it->second;
+  }
+  return pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s);
+}
+
+// After the device has been synchronised.
+static void scratch_trim() {
+  std::lock_guard<std::mutex> lk(g_scratch_mu);
+  for (auto& kv : g_scratch)
+    if (kv.second) (void)hipMemPoolTrimTo(kv.second, 0);
+}
+
 // ---------------------------------------------------------------- handles
 
 struct dock_pocket_s {
@@ -488,6 +535,7 @@ int dock_free_pocket(dock_pocket_t p) try {
                                 " live run(s): free the runs first");
   drop_tables_with(p);
   (void)hipDeviceSynchronize();
+  scratch_trim();
   free_pocket_device(p);
   delete p;
   return DOCK_OK;
@@ -968,7 +1016,10 @@ int dock_free_ligands(dock_ligands_t L) try {
   if (L->n_runs.load() > 0)
     return fail(DOCK_E_ARG, "ligand handle is still used by " + std::to_string(L->n_runs.load()) +
                                 " live run(s): free the runs first");
-  if (!L->host_only) (void)hipDeviceSynchronize();
+  if (!L->host_only) {
+    (void)hipDeviceSynchronize();
+    scratch_trim();
+  }
   free_ligand_device(L);
   delete L;
   return DOCK_OK;
@@ -1046,9 +1097,10 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
 // ================================================================ differentiable form
 
 // Poses from which the adjoint with float atomics takes scratch all the same:
-// 2,048 poses of 64 ligands with Vina terms take 272 us with every atomic in
-// dL/dG and dL/dw, 115 through the sums, whose passes cost some 40 us.
-constexpr int64_t kSumPoses = 256;
+// with Vina terms 512 poses take 79 us back to back either way (90 and 96
+// after a synchronisation), 2,048 some 250 with every atomic in dL/dG and
+// 110 through the sums, whose passes cost some 40 us.
+constexpr int64_t kSumPoses = 768;
 
 static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligands_t L, int64_t n_poses,
                       const int32_t* pose_lig, const float* q, int32_t q_stride, const float* xyz,
@@ -1136,7 +1188,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   const size_t wk_bytes = per_pose_w ? round16(sizeof(int) * size_t(n_poses)) : 0;
   const size_t bound_bytes = sizeof(unsigned) * kBoundWords, flag_words = (bound_bytes + size_t(units) + 3) / 4;
   unsigned char* mem = nullptr;
-  hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&mem), sum_bytes + wp_bytes + wk_bytes + 4 * flag_words, s);
+  hipError_t e = scratch_alloc(reinterpret_cast<void**>(&mem), sum_bytes + wp_bytes + wk_bytes + 4 * flag_words, s);
   if (e != hipSuccess && !deterministic) {
     (void)hipGetLastError();  // no memory for the scratch: float atomics
     a.fixed = 0;
@@ -2213,7 +2265,7 @@ int dock_pocket_map_adjoint(dock_pocket_t p, const float* dLdG, float* dLdxyz, d
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (p->n_rec > 0 && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-      hipMallocAsync(reinterpret_cast<void**>(&a.mask), size_t(map_adjoint_bricks(a.grid)) * 8, s) != hipSuccess) {
+      scratch_alloc(reinterpret_cast<void**>(&a.mask), size_t(map_adjoint_bricks(a.grid)) * 8, s) != hipSuccess) {
     (void)hipGetLastError();
     a.mask = nullptr;
   }

@@ -713,9 +713,17 @@ DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* s
 #pragma unroll
     for (int k = 0; k < K; ++k) a.w_pose[pose * K + k] = dLdE * ek[k];
     a.w_pocket[pose] = pi;
-  } else if (r == 0 && a.dLdw) {
+  } else if (a.dLdw) {
+    // poses of one pocket that share a wave add up first: atomics on one
+    // address take their turns
+    const bool one = LPP < 64 && __builtin_amdgcn_ballot_w64(pi == __builtin_amdgcn_readfirstlane(pi)) == ~0ull;
 #pragma unroll
-    for (int k = 0; k < K; ++k) atomicAdd(&a.dLdw[pi * K + k], dLdE * ek[k]);
+    for (int k = 0; k < K; ++k) {
+      float v = dLdE * ek[k];
+      if (one)
+        for (int o = LPP; o < 64; o <<= 1) v += __shfl_xor(v, o);
+      if (one ? threadIdx.x == 0 : r == 0) atomicAdd(&a.dLdw[pi * K + k], v);
+    }
   }
   if (a.dLdx) {
 #pragma unroll
