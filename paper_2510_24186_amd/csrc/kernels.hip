@@ -713,17 +713,9 @@ DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* s
 #pragma unroll
     for (int k = 0; k < K; ++k) a.w_pose[pose * K + k] = dLdE * ek[k];
     a.w_pocket[pose] = pi;
-  } else if (a.dLdw) {
-    // poses of one pocket that share a wave add up first: atomics on one
-    // address take their turns
-    const bool one = LPP < 64 && __builtin_amdgcn_ballot_w64(pi == __builtin_amdgcn_readfirstlane(pi)) == ~0ull;
+  } else if (r == 0 && a.dLdw) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      float v = dLdE * ek[k];
-      if (one)
-        for (int o = LPP; o < 64; o <<= 1) v += __shfl_xor(v, o);
-      if (one ? threadIdx.x == 0 : r == 0) atomicAdd(&a.dLdw[pi * K + k], v);
-    }
+    for (int k = 0; k < K; ++k) atomicAdd(&a.dLdw[pi * K + k], dLdE * ek[k]);
   }
   if (a.dLdx) {
 #pragma unroll
