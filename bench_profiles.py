@@ -29,7 +29,6 @@ import sqlite3
 ROOT = os.path.dirname(os.path.abspath(__file__))
 SIMDS, CUS, CLK = 1024, 256, 2.4e9
 COPY_KIB = 262144.0          # the calibration copy: 256 MiB each way
-N_BUCKET_LAUNCHES = 6        # MC-step launches of the mixed-pocket step (one per lane bucket)
 
 CMD_INPUTS = ("python bench.py --inputs /tmp/c5.pkl --steps 1 --warmup 0 --no-plain --no-cpu-baseline "
               "--no-extras")
@@ -76,7 +75,7 @@ def trace_summaries(runs, out):
              "`python bench_profiles.py` wrote this file):", "",
              "    " + CMD_INPUTS, "    " + CMD_TRACE, "",
              "One step: 16 map rebuilds, the batched sampler over 65,536 ligands (64 trajectories x 200 MC steps x",
-             "10 Adam steps, 9.23 G evaluations) as six lane-bucket launches on concurrent streams, grouped by",
+             "10 Adam steps, 9.23 G evaluations) as five lane-bucket launches on concurrent streams, grouped by",
              "occupancy class, best poses, and",
              "the deterministic adjoint of the summed best-pose energies to every pocket's maps and weights; then",
              "the differentiation workload (2,048 poses, Vina-form terms) forward and adjoint, twice.", "",
@@ -94,8 +93,8 @@ def trace_summaries(runs, out):
     key = "sample_kernel<%s, %s, 256" % tuple(dom["kernel"].split("<")[1].split(",")[:2])
     grid_threads = [b["grid"] for b in dom["buckets"] if abs(b["ms"] - dom["launch_ms"]) < 1e-3][0] * 256
     dom_trace = [d for n, g, wg, d, lds, scr, st in rows if key in short(n) and g == grid_threads][-1] / 1e6
-    lines += ["", "The first six dispatches draw and score the initial poses; the next six are the MC-step "
-              "launches of", "the six buckets, concurrent within each occupancy class (three blocks per CU, "
+    lines += ["", "The first five dispatches draw and score the initial poses; the next five are the MC-step "
+              "launches of", "the five buckets, concurrent within each occupancy class (three blocks per CU, "
               "then two).  The dominant", "launch (most algorithmic work) is", "`%s, 0, false>` with grid %d threads: %.3f ms here;" % (key, grid_threads, dom_trace),
               "bench.py measured the same launch with HIP events on its stream as %.3f ms (`roofline.launch_ms`)."
               % dom["launch_ms"], "",
@@ -153,7 +152,10 @@ def launch_records(A, B, cal_f, cal_w):
     sa = sorted((d for d in A.values() if "sample_kernel" in d["name"]), key=lambda d: -d["dur_ms"])
     sb = [d for d in B.values() if "sample_kernel" in d["name"]]
     recs = []
-    for da in sa[:N_BUCKET_LAUNCHES]:
+    steps = {}                   # the longest launch of each bucket: the MC steps, not the initial poses
+    for da in sa:
+        steps.setdefault((da["name"], da["grid"]), da)
+    for da in steps.values():
         db_ = min((d for d in sb if d["name"] == da["name"] and d["grid"] == da["grid"]),
                   key=lambda d: abs(d["dur_ms"] - da["dur_ms"]))
         ms = da["dur_ms"]
