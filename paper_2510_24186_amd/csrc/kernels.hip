@@ -919,8 +919,10 @@ struct ExpandArgs {
 
 // dL/dG[t][k] += the term's sum, or w_k S[t]: 16 lanes per marked unit, which
 // reads its part of the sums once and reads and writes its part of dL/dG
-// once.  Where the fixed-point scale says a bound was not finite, every entry
-// of the pocket becomes NaN.
+// once.  Float sums are added atomically, as float contributions are in calls
+// without sums: calls on several streams may add to one buffer.  Where the
+// fixed-point scale says a bound was not finite, every entry of the pocket
+// becomes NaN.
 template <int K>
 __global__ void __launch_bounds__(256) adj_expand_kernel(ExpandArgs e, long long u0, long long u1) {
   const TermsArgs& a = e.t;
@@ -960,7 +962,7 @@ __global__ void __launch_bounds__(256) adj_expand_kernel(ExpandArgs e, long long
                        const float v = static_cast<const float*>(a.sum)[u * kSumUnit + at];
                        if (v == 0.f) return;  // no atom reaches the node
 #pragma unroll
-                       for (int k = 0; k < K; ++k) dst[k * nodes] += a.w[p * K + k] * v;
+                       for (int k = 0; k < K; ++k) atomicAdd(dst + k * nodes, a.w[p * K + k] * v);
                      }
                    });
 }
@@ -978,7 +980,8 @@ hipError_t launch_adj_expand(const TermsArgs& a, const GridDev* grids, int K, lo
 }
 
 // One workgroup per (pocket, term): thread t sums poses t, t + 1024, ... in
-// order, then a fixed tree over the workgroup.
+// order, then a fixed tree over the workgroup; added atomically, so that calls
+// on several streams may add to one dL/dw.
 __global__ void __launch_bounds__(1024) adj_wreduce_kernel(const float* __restrict__ w_pose,
                                                            const int* __restrict__ w_pocket, long long n_poses,
                                                            int K, float* dLdw) {
@@ -996,7 +999,7 @@ __global__ void __launch_bounds__(1024) adj_wreduce_kernel(const float* __restri
     if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) dLdw[pi * K + k] += red[0];
+  if (threadIdx.x == 0) atomicAdd(dLdw + pi * K + k, red[0]);
 }
 
 hipError_t launch_adj_wreduce(const float* w_pose, const int* w_pocket, long long n_poses, int n_pockets, int K,
