@@ -1350,20 +1350,15 @@ struct Scatter {
   double scale = 0.0;                   // fixed: 2^(62 - e) (0: a non-finite bound, nothing is added)
 };
 
-// Marks the units that hold a corner of the cell around x, with a margin of a
-// hundredth of a cell (two kernels' positions may differ in the last bits).
-DK_INLINE void mark_units(unsigned char* flag, const SumGrid& sg, const GridDev& g, int type, const float (&x)[3]) {
+// Marks the units that hold a corner of the cell around any point within err
+// of x (per axis): the marking kernel's positions and the scattering kernel's
+// need not have the same bits.
+DK_INLINE void mark_units(unsigned char* flag, const SumGrid& sg, const GridDev& g, int type, const float (&x)[3],
+                          const float (&err)[3]) {
   int lo[3], hi[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    float pc, f;
-    bool in;
-    int cell;
-    cell_axis<true>(x[c], g.origin[c], g.hi[c], g.inv_spacing, g.dims[c], pc, in, cell, f);
-    const float u = (pc - g.origin[c]) * g.inv_spacing;
-    lo[c] = min(max(min(int(u - 0.01f), cell), 0), g.dims[c] - 1);
-    hi[c] = min(max(int(u + 0.01f), cell) + 1, g.dims[c] - 1);
-  }
+  for (int c = 0; c < 3; ++c)
+    corner_range(x[c], err[c], g.origin[c], g.hi[c], g.inv_spacing, g.dims[c], lo[c], hi[c]);
   for (int z = lo[2] / kSumZ; z <= hi[2] / kSumZ; ++z)
     for (int y = lo[1] / kSumY; y <= hi[1] / kSumY; ++y)
       for (int b = lo[0] / kSumX; b <= hi[0] / kSumX; ++b)

@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <cmath>
 #include <string>
 #include <vector>
 
@@ -117,6 +119,25 @@ struct GridDev {
   int dims[3];
   float hi[3];
 };
+
+// Nodes [first, last] along one axis (o .. hi, n nodes) that can be corners of
+// the cell of a point that lies within err of p, with a margin of a hundredth
+// of a cell for the rounding of the cell coordinate itself.
+__host__ __device__ inline void corner_range(float p, float err, float o, float hi, float inv_h, int n, int& first,
+                                             int& last) {
+  const float a = fminf(fmaxf(p - err, o), hi), b = fminf(fmaxf(p + err, o), hi);
+  const int f = int((a - o) * inv_h - 0.01f), l = int((b - o) * inv_h + 0.01f);
+  first = f < 0 ? 0 : (f > n - 2 ? n - 2 : f);
+  last = (l < 0 ? 0 : (l > n - 2 ? n - 2 : l)) + 1;
+}
+// How far two kernels' forward kinematics of one pose can place an atom apart
+// when the compiler fuses their products differently: each of up to seven
+// compositions rounds some eight sums, of coordinates of the world frame
+// (|x|, |T|) in the last one and of the ligand's own (reach: its largest input
+// coordinate about the root centroid, translations several times that) before.
+__host__ __device__ inline float fk_spread(float x, float t, float reach) {
+  return 0x1p-18f * (fabsf(x) + fabsf(t)) + 0x1p-14f * reach;
+}
 
 struct PocketDev {
   GridDev grid;

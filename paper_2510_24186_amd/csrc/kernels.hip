@@ -805,7 +805,8 @@ DK_INLINE void mark_poses(const TermsArgs& a, long long first, unsigned char* sm
   const PocketDev pk = a.pockets[pi];
   LaneLig<APL> L;
   load_lane_lig<LPP, APL>(L, lg, a.L.ligs + lig, a.L.atoms, a.L.frags, a.L.tors, pk, r);
-  float x[APL][3];
+  float x[APL][3], reach = 0.f;
+  Rigid rg{};
   if (XIN) {
 #pragma unroll
     for (int s = 0; s < APL; ++s) {
@@ -815,12 +816,23 @@ DK_INLINE void mark_poses(const TermsArgs& a, long long first, unsigned char* sm
     }
   } else {
     const float q = r < lg.n_dof ? a.q[pose * a.q_stride + r] : 0.f;
-    (void)fk_place<LPP, APL>(L, q, r, x, S.xs);
+    rg = fk_place<LPP, APL>(L, q, r, x, S.xs);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) reach = fmaxf(reach, fabsf(L.fxb[c]));
+#pragma unroll
+    for (int s = 0; s < APL; ++s) reach = fmaxf(fmaxf(reach, fabsf(L.ax[s])), fmaxf(fabsf(L.ay[s]), fabsf(L.az[s])));
+#pragma unroll
+    for (int k = LPP / 2; k > 0; k >>= 1) reach = fmaxf(reach, __shfl_xor(reach, k));
   }
+  const float T[3] = {rg.Tx, rg.Ty, rg.Tz};
   const SumGrid sg = sum_grid(pk.grid);
 #pragma unroll
-  for (int s = 0; s < APL; ++s)
-    if (APL * r + s < lg.n_atoms) mark_units(a.flag + a.unit_off[pi], sg, pk.grid, L.atype[s], x[s]);
+  for (int s = 0; s < APL; ++s) {
+    float err[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) err[c] = XIN ? 0.f : fk_spread(x[s][c], T[c], reach);
+    if (APL * r + s < lg.n_atoms) mark_units(a.flag + a.unit_off[pi], sg, pk.grid, L.atype[s], x[s], err);
+  }
 }
 
 template <bool XIN>
