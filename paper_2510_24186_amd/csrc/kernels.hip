@@ -696,7 +696,12 @@ DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* s
   Scatter sc;
   if (ADJ && a.dLdG[pi]) {
     const size_t at = size_t(a.unit_off[pi]) * kSumUnit;
-    if (!a.sum) {
+    // (float sums are multiplied by w_k afterwards, where the sum is not zero:
+    // a weight that is not finite has to meet every contribution, zeros too)
+    bool finite_w = true;
+#pragma unroll
+    for (int k = 0; k < K; ++k) finite_w &= fabsf(w[k]) <= FLT_MAX;
+    if (!a.sum || (!a.fixed && !finite_w)) {
       sc.direct = a.dLdG[pi];
     } else if (a.fixed) {
       sc.fixed = static_cast<unsigned long long*>(a.sum) + at * K;

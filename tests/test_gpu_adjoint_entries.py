@@ -73,3 +73,31 @@ def test_every_entry(preset, offset, n):
     held.zero_()
     g.replay()
     assert float(((held.double() - ref).abs() - (n + 8) * 2.0 ** -24 * mag).max()) <= 0
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_a_weight_that_is_not_finite_meets_every_contribution(bad):
+    """deterministic = 0: the entries that a non-finite weight reaches are the
+    same in one call as in small ones, poses with dL/dE = 0 included."""
+    D = G.lib()
+    G.say("adjoint entries: weight", bad)
+    pk = synth.make_pocket(300, grid=33, seed=9)
+    p = G.load_pocket(pk, P.PRESET_TRIDS, keep=True)
+    L = synth.pack_ligands([synth.make_ligand(30, 6, np.random.default_rng(70))])
+    L.pocket_index = np.zeros(1, np.int32)
+    H = G.load_ligands(L)
+    rng = np.random.default_rng(5)
+    n = 1500
+    q = np.zeros((n, H.q_stride), np.float32)
+    q[:, :3] = rng.uniform(-3, 3, (n, 3))
+    q[:, 3:] = rng.uniform(-np.pi, np.pi, (n, H.q_stride - 3))
+    lig, q = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.tensor(q, device="cuda")
+    c = torch.tensor(np.where(rng.random(n) < 0.9, 0.0, 1.0).astype(np.float32), device="cuda")
+    w = torch.tensor(G.weights32(P.PRESET_TRIDS)[None], device="cuda")
+    w[0, 1] = bad
+    one, parts = (torch.zeros((8, p.n_terms) + p.dims[::-1], device="cuda") for _ in range(2))
+    D.dock_score_adjoint(p, H, lig, w, c, q=q, dLdG=[one])
+    for k in range(0, n, 100):
+        D.dock_score_adjoint(p, H, lig[k:k + 100], w, c[k:k + 100], q=q[k:k + 100], dLdG=[parts])
+    assert torch.equal(torch.isnan(one), torch.isnan(parts)) and torch.equal(torch.isinf(one), torch.isinf(parts))
+    assert bool(torch.isnan(one).any())
