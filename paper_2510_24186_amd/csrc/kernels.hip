@@ -327,14 +327,14 @@ __global__ void __launch_bounds__(256) map_adjoint_kernel(MapAdjArgs a) {
     }
     // largest clash distance and hydrogen-bond cutoff: 3.8 A
     if (d2 < 3.81f * 3.81f) {
-      const double inv_d = d > 0.1 ? 1.0 / d : 0.0;
+      const double inv_d = 1.0 / d;
       const float c26 = float(2.6);
 #pragma unroll
       for (int t = 0; t < kTypes; ++t) {
         const bool hb = (hbm >> t) & 1u;
         if (hb ? d2 < c26 * c26 : d2 < dc2[kRadClass[t]]) {
           const double l1 = lt[(long long)(3 * t + 1) * nodes];
-          dphi -= l1 * inv_d;
+          dphi -= d > 0.1 ? l1 * inv_d : 0.0;  // flat below (a lambda may be infinite)
           if (hb)
             dc_h += l1 / 2.6;
           else
