@@ -1325,6 +1325,17 @@ DK_INLINE unsigned long long rank_key(float v, int idx) {
   return (static_cast<unsigned long long>(u) << 32) | static_cast<uint32_t>(idx);
 }
 
+// rank_key of a candidate, from which its energy comes back bit for bit (the
+// lowest bit marks -0.0): a caller may let the outputs take the place of the
+// energies, which are not read again once they are sorted.
+DK_INLINE unsigned long long best_key(float e, int idx) {
+  return rank_key(e, int(uint32_t(idx) << 1 | (__float_as_uint(e) == 0x80000000u ? 1u : 0u)));
+}
+DK_INLINE float best_energy(unsigned long long key) {
+  const uint32_t u = uint32_t(key >> 32);
+  return __uint_as_float((key & 1u) ? 0x80000000u : ((u & 0x80000000u) ? u ^ 0x80000000u : ~u));
+}
+
 // RMSD^2 sum of the lane's atoms against a pose in LDS.
 template <int APL>
 DK_INLINE float sq_diff(const float (&x)[APL][3], const float4* y, int n_atoms, int r) {
@@ -1368,7 +1379,7 @@ __global__ void __launch_bounds__(64 * W) best_kernel(BestArgs a) {
   for (int i = tid; i < a.t_pad; i += 64 * W) {
     float e = i < T ? a.E_best[size_t(lig) * T + i] : INFINITY;
     if (!(e < INFINITY)) e = INFINITY;  // NaN and +inf rank last
-    key[i] = rank_key(e, i < T ? i : 0x7fffffff);
+    key[i] = best_key(e, i < T ? i : 0x7fffffff);
   }
   auto sync = [] {
     if (W > 1)
@@ -1394,7 +1405,7 @@ __global__ void __launch_bounds__(64 * W) best_kernel(BestArgs a) {
   const float inv_n = 1.0f / float(lg.n_atoms);
   auto near = [&](float acc) { return sqrtf(group_sum<64>(acc) * inv_n) < a.rmsd_cut; };
   // this wave's candidate of the next turn: read ahead of the comparisons
-  auto cand_of = [&](int c) { return c < T && key[c] < inf_key ? int(uint32_t(key[c])) : -1; };
+  auto cand_of = [&](int c) { return c < T && key[c] < inf_key ? int(uint32_t(key[c]) >> 1) : -1; };
   auto q_of = [&](int t) {
     return t >= 0 && r < lg.n_dof ? a.q_best[(size_t(lig) * T + t) * a.q_stride + r] : 0.f;
   };
@@ -1459,7 +1470,7 @@ __global__ void __launch_bounds__(64 * W) best_kernel(BestArgs a) {
         }
       }
       if (r == 0) {
-        const float E = a.E_best[size_t(lig) * T + t];
+        const float E = best_energy(key[c + wv]);
         if (a.E_out) a.E_out[o] = E;
         if (a.E_screen) a.E_screen[o] = E / (1.0f + a.w_tor * float(lg.n_tors));
         if (a.idx_out) a.idx_out[o] = t;
