@@ -1417,14 +1417,16 @@ __global__ void __launch_bounds__(64 * W) best_kernel(BestArgs a) {
     float x[APL][3];
     fk_place_shfl<LPP, APL>(L, q, r, x);
     bool dup = t < 0;
-    for (int k = 0; k < n_kept && !dup; k += 4) {
+    int k = 0;
+    for (; k + 4 <= n_kept && !dup; k += 4) {
       // four at a time: their sums and square roots overlap
       float acc[4];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) acc[m] = sq_diff<APL>(x, kept + size_t(min(k + m, n_kept - 1)) * a.max_atoms, lg.n_atoms, r);
+      for (int m = 0; m < 4; ++m) acc[m] = sq_diff<APL>(x, kept + size_t(k + m) * a.max_atoms, lg.n_atoms, r);
 #pragma unroll
       for (int m = 0; m < 4; ++m) dup |= near(acc[m]);
     }
+    for (; k < n_kept && !dup; ++k) dup = near(sq_diff<APL>(x, kept + size_t(k) * a.max_atoms, lg.n_atoms, r));
     if (W > 1) {
 #pragma unroll
       for (int s = 0; s < APL; ++s)
@@ -1499,10 +1501,21 @@ hipError_t launch_best(const BestArgs& a, hipStream_t s) {
   auto lds = [&](int waves) {
     return (size_t(a.t_pad) * 8 + 15) / 16 * 16 + size_t(a.top_n + (waves > 1 ? waves : 0)) * a.max_atoms * 16;
   };
-  // four waves per ligand until the ligands alone fill the chip several times
-  // (x 64 candidates: 4,096 ligands 122 us with four, 147 with one; 16,384 398
-  // and 335), where the LDS allows
-  if (a.n_ligands <= 4096 && lds(4) <= 64 * 1024)
+  // Four waves per ligand share a turn's placement and comparisons, one wave
+  // spends less on a workgroup and stops at its first kept pose.  So four where
+  // there are several poses to keep and a CU holds few ligands (by their number
+  // and by the LDS): a turn's waves then overlap what the ligands alone leave
+  // idle.  Or a long sort, where few ligands wait for it.  Far-apart candidates,
+  // us with one wave and with four: 64 candidates, best 8: 512 ligands 27.3 and
+  // 14.7, 2,048 32.0 and 30.0, 4,096 47.0 and 50.3; best 24 of 4,096 (six
+  // ligands a CU by their LDS) 332 and 167; best 1 of 1,024 8.3 and 11.9, of
+  // 4,096 11.0 and 30.9; 256 candidates, best 1: 512 ligands 14.0 and 13.3,
+  // 2,048 16.1 and 25.3.
+  constexpr int kCus = 256;
+  const int resident = int(std::min<size_t>((size_t(a.n_ligands) + kCus - 1) / kCus, 160 * 1024 / lds(1)));
+  const bool four = (a.top_n >= std::max(4, resident)) || (a.top_n >= 2 && resident <= 1) ||
+                    (a.n_traj >= 256 && resident <= 2);
+  if (four && lds(4) <= 64 * 1024)
     hipLaunchKernelGGL(best_kernel<4>, dim3(a.n_ligands), dim3(256), lds(4), s, a);
   else
     hipLaunchKernelGGL(best_kernel<1>, dim3(a.n_ligands), dim3(64), lds(1), s, a);
