@@ -1043,6 +1043,10 @@ DK_INLINE float wrap_clamp(float q, int r, const LaneLig<APL>& L) {
 // per pass, 256 ligands of 10-60 atoms x 128 trajectories x 100 steps went
 // from 46.8 to 43.0 ms, 2,048 ligands of 10-70 atoms in 16 pockets x 64 x 30
 // from 83.2 to 65.1 ms (the kernel is bound by VALU issue, then LDS).
+// The FULL kernel has one evaluation site for its first-order rules and its line
+// search: with one for each it spilled 264 bytes a lane (two atoms per lane), now
+// 176, and 512 ligands of 10-60 atoms x 64 x 3 line-searched steps took 6.62 ms,
+// now 5.66 (logged Adam steps: 2.12 and 1.82).
 template <int LPP, int APL, int MODE, bool FULL>
 DK_INLINE void run_traj(const SampleArgs& a, LaneLig<APL>& L, const PocketDev& pk, const MdnArg& mdn,
                         const PairRec* pairs,
@@ -1092,83 +1096,79 @@ DK_INLINE void run_traj(const SampleArgs& a, LaneLig<APL>& L, const PocketDev& p
     const int j = int(__umulhi(w.x, uint32_t(L.n_dof)));
     float qn = q;
     if (r == j) qn = L.lo + (L.hi - L.lo) * u01(w.y);
-    float E;
-    if (!FULL || a.local_opt != DOCK_LOCAL_LINESEARCH) {
-      // n_local gradient evaluations with a first-order update after each
-      // (Adam by default; the Table S5 alternatives otherwise), then the
-      // energy of the refined pose (FULL: one evaluation site, n_local + 1
-      // calls)
-      float m = 0.f, v = 0.f, b1t = 1.f, b2t = 1.f;
-      for (int t = 0;; ++t) {
-        if (!FULL && t == a.n_local) {
-          E = eval_pose<LPP, APL, kWantE, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn).E;
-          record(qn, 0.f, E);
-          break;
-        }
-        const EvalOut o =
-            eval_pose<LPP, APL, FULL ? kWantBoth : kWantG, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn);
-        record(qn, o.g, o.E);
-        E = o.E;
-        if (FULL && t == a.n_local) break;
-        const float g = o.g;
-        // square roots and quotients on the hardware units (about 1 ulp;
-        // the IEEE-exact sequences cost ~12 instructions each)
-        float step;
-        if (a.local_opt == DOCK_LOCAL_SGD) {
-          step = a.lr * g;
-        } else if (a.local_opt == DOCK_LOCAL_RMSPROP) {
-          v = a.rms_alpha * v + (1.f - a.rms_alpha) * g * g;
-          step = a.lr * g * rcp_hw(sqrt_hw(v) + a.eps);
-        } else if (a.local_opt == DOCK_LOCAL_ADAGRAD) {
-          v += g * g;
-          step = a.lr * g * rcp_hw(sqrt_hw(v) + a.eps);
-        } else {
-          if (a.local_opt == DOCK_LOCAL_ADAMW) qn *= 1.f - a.lr * a.weight_decay;
-          m = a.b1 * m + (1.f - a.b1) * g;
-          v = a.b2 * v + (1.f - a.b2) * g * g;
-          b1t *= a.b1;
-          b2t *= a.b2;
-          const float mh = m * rcp_hw(1.f - b1t), vh = v * rcp_hw(1.f - b2t);
-          step = a.lr * mh * rcp_hw(sqrt_hw(vh) + a.eps);
-        }
-        if (dof) qn = wrap_clamp(qn - step, r, L);
+    float E = 0.f;
+    // first-order update of qn from the gradient g (Adam by default; the Table
+    // S5 alternatives otherwise)
+    float m = 0.f, v = 0.f, b1t = 1.f, b2t = 1.f;
+    auto update = [&](float g) {
+      // square roots and quotients on the hardware units (about 1 ulp;
+      // the IEEE-exact sequences cost ~12 instructions each)
+      float step;
+      if (a.local_opt == DOCK_LOCAL_SGD) {
+        step = a.lr * g;
+      } else if (a.local_opt == DOCK_LOCAL_RMSPROP) {
+        v = a.rms_alpha * v + (1.f - a.rms_alpha) * g * g;
+        step = a.lr * g * rcp_hw(sqrt_hw(v) + a.eps);
+      } else if (a.local_opt == DOCK_LOCAL_ADAGRAD) {
+        v += g * g;
+        step = a.lr * g * rcp_hw(sqrt_hw(v) + a.eps);
+      } else {
+        if (a.local_opt == DOCK_LOCAL_ADAMW) qn *= 1.f - a.lr * a.weight_decay;
+        m = a.b1 * m + (1.f - a.b1) * g;
+        v = a.b2 * v + (1.f - a.b2) * g * g;
+        b1t *= a.b1;
+        b2t *= a.b2;
+        const float mh = m * rcp_hw(1.f - b1t), vh = v * rcp_hw(1.f - b2t);
+        step = a.lr * mh * rcp_hw(sqrt_hw(vh) + a.eps);
       }
+      if (dof) qn = wrap_clamp(qn - step, r, L);
+    };
+    if (!FULL) {
+      for (int t = 0; t < a.n_local; ++t) {
+        update(eval_pose<LPP, APL, kWantG, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn).g);
+        ++nev;
+      }
+      E = eval_pose<LPP, APL, kWantE, false, MODE>(L, qn, pk, pairs, S, r, nullptr, nullptr, mdn).E;
+      ++nev;
     } else {
-      // Armijo line search as a loop over trial poses (one evaluation site):
-      // the first call scores the perturbed pose; each search tries
-      // alpha = 1, 1/2, ..., 2^-10 along -g/|g|; a failed search ends the
-      // refinement
-      float g = 0.f, d = 0.f, slope = 0.f, alpha = 1.f;
-      float qtry = qn;
-      int done_steps = 0, halvings = 0;
-      bool first = true;
-      E = 0.f;
+      // one evaluation site for both rules.  First order: n_local gradient
+      // evaluations with an update after each, then the energy of the refined
+      // pose.  Armijo line search as a loop over trial poses: the first call
+      // scores the perturbed pose; each search tries alpha = 1, 1/2, ...,
+      // 2^-10 along -g/|g|; a failed search ends the refinement (m, v, b1t:
+      // its gradient, direction and slope)
+      const bool line = a.local_opt == DOCK_LOCAL_LINESEARCH;
+      float qtry = qn, alpha = 1.f;
+      int done_steps = -1, halvings = 0;
       for (;;) {
         const EvalOut o = eval_pose<LPP, APL, kWantBoth, false, MODE>(L, qtry, pk, pairs, S, r, nullptr, nullptr, mdn);
         record(qtry, o.g, o.E);
-        if (first) {
+        if (!line) {
           E = o.E;
-          g = o.g;
-          first = false;
-        } else if (o.E <= E + 1e-4f * alpha * slope) {
+          if (++done_steps == a.n_local) break;
+          update(o.g);
+          qtry = qn;
+          continue;
+        }
+        if (done_steps < 0 || o.E <= E + 1e-4f * alpha * b1t) {
           qn = qtry;
           E = o.E;
-          g = o.g;
+          m = o.g;
           ++done_steps;
         } else {
           if (++halvings > 10) break;
           alpha *= 0.5f;
-          qtry = dof ? wrap_clamp(qn + alpha * d, r, L) : 0.f;
+          qtry = dof ? wrap_clamp(qn + alpha * v, r, L) : 0.f;
           continue;
         }
         if (done_steps >= a.n_local) break;
-        const float gn = sqrtf(group_sum<LPP>(dof ? g * g : 0.f));
+        const float gn = sqrtf(group_sum<LPP>(dof ? m * m : 0.f));
         if (!(gn > 0.f)) break;
-        d = dof ? -g / gn : 0.f;
-        slope = -gn;
+        v = dof ? -m / gn : 0.f;
+        b1t = -gn;
         alpha = 1.f;
         halvings = 0;
-        qtry = dof ? wrap_clamp(qn + d, r, L) : 0.f;
+        qtry = dof ? wrap_clamp(qn + v, r, L) : 0.f;
       }
     }
     const float u = u01(w.z);
