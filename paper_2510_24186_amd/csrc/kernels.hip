@@ -1193,6 +1193,15 @@ DK_INLINE void run_traj(const SampleArgs& a, LaneLig<APL>& L, const PocketDev& p
   }
 }
 
+// A pointer that is the same in every lane, in scalar registers.
+template <class T>
+DK_INLINE T* wave_uniform(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v)))),
+                 hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))));
+  return reinterpret_cast<T*>(uint64_t(hi) << 32 | lo);
+}
+
 // Three waves per SIMD (168 VGPRs).  With two atoms per lane the step loop
 // needs more and spills a few registers to scratch (served from L2, outside
 // the pair-pass loop); two waves per SIMD without spills measured slower.
@@ -1246,10 +1255,22 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3)))
     __syncthreads();
     const int traj = wi.y + grp;
     if (traj < a.n_traj) {
-      const PocketDev pk = a.pockets[lg.pocket];
+      PocketDev pk = a.pockets[lg.pocket];
+      MdnArg mdn = mdn_for(a.L, lg, pk);
+      if (MODE == kModeGridMdn) {
+        // a workgroup has one ligand: the residue loops' pointers go to scalar
+        // registers (in vector registers they were spilled, and read from
+        // scratch for every residue: 512 ligands x 64 x 3 steps, line search
+        // 46.9 ms so and 40.1 now, Adam 12.4 and 11.1)
+        pk.mcell_start = wave_uniform(pk.mcell_start);
+        pk.mcell_res = wave_uniform(pk.mcell_res);
+        pk.res_range = wave_uniform(pk.res_range);
+        pk.res_xyz = wave_uniform(pk.res_xyz);
+        mdn.par = wave_uniform(mdn.par);
+      }
       LaneLig<APL> L;
       load_lane_lig<LPP, APL>(L, lg, a.L.ligs + lig, a.L.atoms, a.L.frags, a.L.tors, pk, r);
-      run_traj<LPP, APL, MODE, FULL>(a, L, pk, mdn_for(a.L, lg, pk), sp, S, lig, traj, r);
+      run_traj<LPP, APL, MODE, FULL>(a, L, pk, mdn, sp, S, lig, traj, r);
     }
     __syncthreads();
   }
