@@ -284,7 +284,7 @@ typedef struct {
   uint32_t seed;
   int32_t form;             /* DOCK_FORM_PLAIN: one launch per ligand;
                                DOCK_FORM_BATCHED: ragged-packed persistent launches */
-  int32_t use_graph;        /* batched: replay a launch sequence that comes again as a hipGraph */
+  int32_t use_graph;        /* batched: replay the launch sequence as a hipGraph */
   int32_t steps_per_launch; /* 0: all steps in one launch per bucket */
   int32_t record_trace;     /* store q, E, dE/dq of every evaluation (tests) */
   int32_t lanes_per_pose;   /* 0: planner choice; else 16, 32 or 64: a wider group
@@ -309,10 +309,12 @@ void dock_sample_params_default(dock_sample_params* p);
  * streams forked from `stream` and joined back into it.  The library keeps
  * a pool of side streams per device for the life of the process, shared by
  * all runs.  Runs are created, advanced, restarted and freed from one host
- * thread at a time: with use_graph = 1 (the default) an MC-step phase of as
- * many steps as the one before it is captured as a graph through the shared
- * side streams (a run that is advanced once captures none), and runs used
- * from several threads at once are not supported.
+ * thread at a time: with use_graph = 1 (the default) dock_sample launches its
+ * MC steps and then captures the same launches as a graph, through the shared
+ * side streams, which dock_run_restart replays (a dock_run_advance of another
+ * step count is captured when it comes twice in a row), and runs used from
+ * several threads at once are not supported.  On a stream that is being
+ * captured, restarts and advances enqueue their kernels themselves.
  * A run's ligands of 33-64 atoms are laid out two atoms per lane when its
  * trajectories of such ligands fill at least two waves per wave slot of the
  * device (two poses per wavefront), else one atom per lane. */

@@ -1322,7 +1322,8 @@ struct dock_run_s {
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
   int graph_steps = -1;             // steps of the captured graph
-  int eager_steps = -1;             // steps of the last phase launched without it
+  bool graph_launched = false;
+  int eager_steps = -1;             // steps of the last phase launched without one
   // per-launch timing of the last call (eager launches only)
   struct Launch {
     dock_launch_stat st;
@@ -1528,50 +1529,64 @@ static hipError_t enqueue_phase(dock_run_s* r, bool init, int steps, hipStream_t
   return e;
 }
 
+static void drop_graph(dock_run_s* r) {
+  if (r->gexec) (void)hipGraphExecDestroy(r->gexec);
+  if (r->graph) (void)hipGraphDestroy(r->graph);
+  r->gexec = nullptr;
+  r->graph = nullptr;
+  r->graph_steps = -1;
+  r->graph_launched = false;
+}
+
+// Captures the launches of a phase of `steps` MC steps as the run's graph.
+static int capture_phase(dock_run_s* r, int steps) {
+  drop_graph(r);
+  hipStream_t cs = nullptr;
+  HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+  hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+  if (e == hipSuccess) {
+    const bool rec = r->recording;
+    r->recording = false;
+    hipError_t e2 = enqueue_phase(r, false, steps, cs);
+    r->recording = rec;
+    e = hipStreamEndCapture(cs, &r->graph);
+    if (e2 != hipSuccess) e = e2;
+  }
+  if (e == hipSuccess) e = hipGraphInstantiate(&r->gexec, r->graph, nullptr, nullptr, 0);
+  (void)hipStreamDestroy(cs);
+  if (e != hipSuccess) return fail(DOCK_E_HIP, std::string("graph capture: ") + hipGetErrorString(e));
+  r->graph_steps = steps;
+  return DOCK_OK;
+}
+
+static bool uses_graph(const dock_run_s* r) { return r->p.use_graph && r->p.form == DOCK_FORM_BATCHED; }
+
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
+// A phase of as many steps as the run's graph replays it.  Other phases are
+// launched as they are, and captured when as many steps come a second time in
+// a row: the capture costs more than the launches it replaces.  (dock_sample
+// captures its own phase after launching it.)  On a stream that is being
+// captured the launches themselves go into the caller's graph.
 static int run_phase(dock_run_s* r, bool init, int steps, hipStream_t s) {
   if (!init && steps == 0) return DOCK_OK;
-  if (!init && r->p.use_graph && r->p.form == DOCK_FORM_BATCHED) {
-    // a phase is captured when it comes a second time: the capture costs more
-    // than the launches it replaces.  (On a stream that is itself being
-    // captured the graph is launched as ever.)
-    if (r->graph_steps != steps && r->eager_steps != steps) {
-      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-        const bool rec = r->recording;
-        r->recording = false;
-        const hipError_t e = enqueue_phase(r, false, steps, s);
-        r->recording = rec;
-        HIP_TRY(e);
-        r->eager_steps = steps;
-        r->step += steps;
-        return DOCK_OK;
-      }
-    }
+  if (!init && uses_graph(r) && !capturing(s) && (r->graph_steps == steps || r->eager_steps == steps)) {
     if (r->graph_steps != steps) {
-      if (r->gexec) (void)hipGraphExecDestroy(r->gexec);
-      if (r->graph) (void)hipGraphDestroy(r->graph);
-      r->gexec = nullptr;
-      r->graph = nullptr;
-      r->graph_steps = -1;
-      hipStream_t cs = nullptr;
-      HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-      hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-      if (e == hipSuccess) {
-        const bool rec = r->recording;
-        r->recording = false;
-        hipError_t e2 = enqueue_phase(r, false, steps, cs);
-        r->recording = rec;
-        e = hipStreamEndCapture(cs, &r->graph);
-        if (e2 != hipSuccess) e = e2;
-      }
-      if (e == hipSuccess) e = hipGraphInstantiate(&r->gexec, r->graph, nullptr, nullptr, 0);
-      (void)hipStreamDestroy(cs);
-      if (e != hipSuccess) return fail(DOCK_E_HIP, std::string("graph capture: ") + hipGetErrorString(e));
-      r->graph_steps = steps;
+      const int rc = capture_phase(r, steps);
+      if (rc != DOCK_OK) return rc;
     }
     HIP_TRY(hipGraphLaunch(r->gexec, s));
+    r->graph_launched = true;
   } else {
-    HIP_TRY(enqueue_phase(r, init, steps, s));
+    const bool rec = r->recording;
+    r->recording = rec && (init || !uses_graph(r));
+    const hipError_t e = enqueue_phase(r, init, steps, s);
+    r->recording = rec;
+    HIP_TRY(e);
+    if (!init) r->eager_steps = steps;
   }
   if (!init) r->step += steps;
   return DOCK_OK;
@@ -1861,8 +1876,8 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   r->n_queue = int(r->buckets.size()) * std::max(1, (p->n_steps + chunk - 1) / chunk) * r->n_part;
   // one allocation: what starts as zeros, the energies and queue (written
   // before they are read), then what is uploaded.  With an allocation, a
-  // clear and a copy for each of these, and a graph captured for a phase that
-  // ran once, a new run of 1,024 trajectories of a 35-atom ligand, 8 steps,
+  // clear and a copy for each of these, and a graph captured before the first
+  // launches, a new run of 1,024 trajectories of a 35-atom ligand, 8 steps,
   // took 575 us with its best poses, of which the host some 200; now 491.
   size_t bytes = 0;
   const auto part = [&](size_t n) {
@@ -1917,6 +1932,8 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   }
   if (e != hipSuccess) return bail(DOCK_E_HIP, std::string("init: ") + hipGetErrorString(e));
   rc = timed_phases(r, true, p->n_steps, s);
+  // the graph that dock_run_restart replays, made while the device works
+  if (rc == DOCK_OK && uses_graph(r) && p->n_steps > 0 && !capturing(s)) rc = capture_phase(r, p->n_steps);
   if (rc != DOCK_OK) {
     std::string m = g_err;
     free_run(r);
@@ -2060,11 +2077,7 @@ int dock_run_advance(dock_run_t r, int32_t n_steps, void* stream) try {
     HIP_TRY(dev_alloc(&r->own_queue, size_t(need)));
     r->d_queue = r->own_queue;
     r->n_queue = need;
-    if (r->gexec) (void)hipGraphExecDestroy(r->gexec);
-    if (r->graph) (void)hipGraphDestroy(r->graph);
-    r->gexec = nullptr;
-    r->graph = nullptr;
-    r->graph_steps = -1;
+    drop_graph(r);
   }
   return timed_phases(r, false, n_steps, s);
 } catch (...) {
@@ -2196,6 +2209,7 @@ int dock_run_plan(dock_run_t r, int32_t* lig_bucket, int32_t* bucket_lanes, int3
 
 int dock_free_run(dock_run_t r) try {
   if (!r) return DOCK_OK;
+  if (!r->graph_launched) drop_graph(r);  // on the host alone, while the device works
   (void)hipDeviceSynchronize();
   free_run(r);
   return DOCK_OK;
