@@ -236,9 +236,12 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
  *   dLdG   host array [n_pockets] of device pointers (entries nullable) or NULL
  *   dLdw   device [n_pockets * K] or NULL;  dLdq, dLdx device or NULL
  * All pockets of a call share one preset; n_pockets <= 16.
- *   deterministic  0: dL/dG by float atomics (summation order, and so the last
- *                     bits, vary from call to call; so does dL/dw in calls of
- *                     fewer than 768 poses);
+ *   deterministic  0: by float atomics (summation order, and so the last bits,
+ *                     vary from call to call); calls on several streams may
+ *                     add to one buffer.  From 1,280 poses (TRIDS terms) or
+ *                     768 (Vina) on the contributions are first collected per
+ *                     call, outside stream capture and where scratch can be
+ *                     had, and dL/dw reduced in a fixed order;
  *                  1: bitwise repeatable.  dL/dG is summed as 64-bit
  *                     integers: every corner contribution is rounded once to
  *                     a multiple of 2^(e - 62), where 2^e bounds any node's
@@ -247,10 +250,13 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
  *                     converted and added to dLdG.  dL/dw is reduced over the
  *                     poses in a fixed order.  Non-finite dLdE or w make
  *                     that pocket's dL/dG NaN.
- *   Scratch is allocated and released on the stream: 8 bytes per dL/dG entry
- *   (deterministic) or 4 bytes per node and type (otherwise, from 768 poses
- *   on and outside stream capture), of which only the surroundings of the
- *   poses' atoms are touched, and 4 (K + 1) bytes per pose.
+ *                     Calls that add to one buffer have to be ordered.
+ *   Scratch: 8 bytes per dL/dG entry (deterministic) or 4 bytes per node and
+ *   type (otherwise), of which only the surroundings of the poses' atoms are
+ *   touched, and 4 (K + 1) bytes per pose.  Up to 128 MiB of it per device are
+ *   kept between calls, of these and of dock_pocket_map_adjoint (1 bit per
+ *   node), until the last pocket and ligand handle is freed; what does not fit
+ *   is allocated and released on the stream.
  * Ligand-internal pair forces are summed in FP64 in a fixed order, or as
  * fixed point, in either mode, so E, dL/dq and dL/dx never depend on timing.
  * ---------------------------------------------------------------------- */

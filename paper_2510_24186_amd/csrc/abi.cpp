@@ -81,49 +81,153 @@ static void dev_free(T*& p) {
 
 // ---------------------------------------------------------------- scratch
 
-// Stream-ordered scratch of the adjoints, from a pool of the library's own
-// per device.  The device's default pool returns its memory at every
-// synchronisation, and a call after one then mapped its scratch anew (a
-// deterministic adjoint of 256 poses: 423 us after a synchronisation, 95
-// back to back).  This one keeps up to kScratchKeep between calls and gives
-// it back when a pocket or ligand handle is freed.
-constexpr uint64_t kScratchKeep = 128ull << 20;
-static std::mutex g_scratch_mu;
-static std::map<int, hipMemPool_t> g_scratch;
-
-static hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t s) {
+static bool capturing(hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  int dev = 0;
-  hipMemPool_t pool = nullptr;
-  if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-      hipGetDevice(&dev) == hipSuccess) {
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    auto it = g_scratch.find(dev);
-    if (it == g_scratch.end()) {
-      hipMemPoolProps props{};
-      props.allocType = hipMemAllocationTypePinned;
-      props.location.type = hipMemLocationTypeDevice;
-      props.location.id = dev;
-      uint64_t keep = kScratchKeep;
-      if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
-        pool = nullptr;
-      } else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-        (void)hipMemPoolDestroy(pool);
-        pool = nullptr;
-      }
-      (void)hipGetLastError();
-      it = g_scratch.emplace(dev, pool).first;
-    }
-    pool = it->second;
-  }
-  return pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s);
+  return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
 }
 
-// After the device has been synchronised.
-static void scratch_trim() {
+// Scratch of the adjoints: blocks kept between calls, at most kScratchKeep
+// bytes per device, until the last pocket or ligand handle is freed.  A block
+// is in one call at a time; the next call on it waits, on its stream, for the
+// event the last one left, so streams and threads may share blocks.  (The null
+// stream outlives every block, so its uses leave no event: one is recorded when
+// another stream takes the block.)  A call takes the smallest free block that
+// its own stream used last, else a new one, else any free one that is large
+// enough.
+// (The runtime's pools do not keep them: the default one returns its memory at
+// every synchronisation, and one with a release threshold of 128 MiB still
+// returned a block at the next synchronisation after a call of another size.
+// Mapping 84 MiB again took 200-400 us of host time; a float adjoint of 2,048
+// poses with Vina terms that took turns with a deterministic one 348 us, 128
+// without the turns.)
+// Requests above the bound, and those on a stream that is being captured, are
+// plain stream-ordered allocations.
+constexpr size_t kScratchKeep = size_t(128) << 20;
+struct ScratchBlock {
+  unsigned char* mem = nullptr;
+  size_t bytes = 0;
+  hipEvent_t done = nullptr;
+  hipStream_t last = nullptr;  // another than the null stream: to prefer among free blocks only,
+                               // its name may be a newer stream's by now
+  bool busy = false;
+};
+static std::mutex g_scratch_mu;
+static std::map<int, std::vector<ScratchBlock*>> g_scratch;
+static std::atomic<int> g_handles{0};  // pockets and ligand sets on a device
+
+struct Scratch {
+  unsigned char* mem = nullptr;
+  ScratchBlock* block = nullptr;  // null: an allocation of this call
+};
+
+// Later work of s comes after the block's last use.
+static hipError_t scratch_wait(ScratchBlock* b, hipStream_t s) {
+  if (!b->last && !s) return hipSuccess;
+  const hipError_t e = b->last ? hipSuccess : hipEventRecord(b->done, nullptr);
+  return e == hipSuccess ? hipStreamWaitEvent(s, b->done, 0) : e;
+}
+
+static void scratch_drop(ScratchBlock* b, hipStream_t s) {
+  (void)scratch_wait(b, s);
+  (void)hipFreeAsync(b->mem, s);
+  (void)hipEventDestroy(b->done);
+  delete b;
+}
+
+// A kept block for `bytes` on stream s (mem stays null where the bound does
+// not allow one).
+static hipError_t scratch_block(size_t bytes, hipStream_t s, Scratch* out) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
   std::lock_guard<std::mutex> lk(g_scratch_mu);
-  for (auto& kv : g_scratch)
-    if (kv.second) (void)hipMemPoolTrimTo(kv.second, 0);
+  std::vector<ScratchBlock*>& v = g_scratch[dev];
+  ScratchBlock *own = nullptr, *any = nullptr;
+  size_t total = 0;
+  for (ScratchBlock* b : v) {
+    total += b->bytes;
+    if (b->busy || b->bytes < bytes) continue;
+    if (!any || b->bytes < any->bytes) any = b;
+    if (b->last == s && (!own || b->bytes < own->bytes)) own = b;
+  }
+  ScratchBlock* b = own;
+  const size_t size = (bytes + (size_t(1) << 20) - 1) >> 20 << 20;
+  if (!b && total + size > kScratchKeep) b = any;
+  if (!b) {
+    // make room: free blocks too small for this call
+    for (size_t k = 0; k < v.size() && total + size > kScratchKeep;) {
+      if (v[k]->busy) {
+        ++k;
+        continue;
+      }
+      total -= v[k]->bytes;
+      scratch_drop(v[k], s);
+      v.erase(v.begin() + long(k));
+    }
+    if (total + size > kScratchKeep) return hipSuccess;
+    v.reserve(v.size() + 1);
+    b = new ScratchBlock;
+    e = hipEventCreateWithFlags(&b->done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipMallocAsync(reinterpret_cast<void**>(&b->mem), size, s);
+    if (e != hipSuccess) {
+      if (b->done) (void)hipEventDestroy(b->done);
+      delete b;
+      return e;
+    }
+    b->bytes = size;
+    v.push_back(b);
+  } else {
+    e = scratch_wait(b, s);
+    if (e != hipSuccess) return e;
+  }
+  b->busy = true;
+  b->last = s;
+  out->mem = b->mem;
+  out->block = b;
+  return hipSuccess;
+}
+
+static hipError_t scratch_take(size_t bytes, hipStream_t s, Scratch* out) {
+  if (bytes <= kScratchKeep && !capturing(s)) {
+    if (scratch_block(bytes, s, out) == hipSuccess && out->mem) return hipSuccess;
+    (void)hipGetLastError();
+  }
+  return hipMallocAsync(reinterpret_cast<void**>(&out->mem), bytes, s);
+}
+
+// After the call's last launch that uses it.
+static void scratch_give(const Scratch& t, hipStream_t s) {
+  if (!t.block) {
+    if (t.mem) (void)hipFreeAsync(t.mem, s);
+    return;
+  }
+  std::lock_guard<std::mutex> lk(g_scratch_mu);
+  if (s && hipEventRecord(t.block->done, s) != hipSuccess) (void)hipStreamSynchronize(s);
+  t.block->busy = false;
+}
+
+// A handle is gone: with the last one, the blocks go (the caller synchronises
+// the device afterwards, which returns the memory).
+static void scratch_handle_freed() {
+  if (g_handles.fetch_sub(1) != 1) return;
+  int cur = 0;
+  if (hipGetDevice(&cur) != hipSuccess) return;
+  std::lock_guard<std::mutex> lk(g_scratch_mu);
+  for (auto& kv : g_scratch) {
+    std::vector<ScratchBlock*> busy;
+    if (kv.first != cur) (void)hipSetDevice(kv.first);
+    for (ScratchBlock* b : kv.second) {
+      if (b->busy)
+        busy.push_back(b);
+      else
+        scratch_drop(b, nullptr);
+    }
+    if (kv.first != cur) {
+      (void)hipDeviceSynchronize();
+      (void)hipSetDevice(cur);
+    }
+    kv.second.swap(busy);
+  }
 }
 
 // ---------------------------------------------------------------- handles
@@ -448,6 +552,7 @@ int dock_load_pocket(const dock_pocket_desc* d, void* stream, dock_pocket_t* out
     pd.tp = p->d_tp;
     pd.M = nullptr;
     pd.G = nullptr;
+    g_handles.fetch_add(1);
     *out = p;
     return DOCK_OK;
   }
@@ -472,6 +577,7 @@ int dock_load_pocket(const dock_pocket_desc* d, void* stream, dock_pocket_t* out
   if (e != hipSuccess) return cleanup(DOCK_E_HIP, std::string("map build: ") + hipGetErrorString(e));
   pd.M = p->d_M;
   pd.G = p->d_G;
+  g_handles.fetch_add(1);
   *out = p;
   return DOCK_OK;
 } catch (...) {
@@ -534,8 +640,8 @@ int dock_free_pocket(dock_pocket_t p) try {
     return fail(DOCK_E_ARG, "pocket is still used by " + std::to_string(p->n_runs.load()) +
                                 " live run(s): free the runs first");
   drop_tables_with(p);
+  scratch_handle_freed();
   (void)hipDeviceSynchronize();
-  scratch_trim();
   free_pocket_device(p);
   delete p;
   return DOCK_OK;
@@ -900,6 +1006,7 @@ int dock_load_ligands(const dock_ligand_desc* d, void* stream, dock_ligands_t* o
       return fail(e == hipErrorOutOfMemory ? DOCK_E_OOM : DOCK_E_HIP,
                   std::string("ligand upload: ") + hipGetErrorString(e));
     }
+    g_handles.fetch_add(1);
   }
   *out = L;
   return DOCK_OK;
@@ -1017,8 +1124,8 @@ int dock_free_ligands(dock_ligands_t L) try {
     return fail(DOCK_E_ARG, "ligand handle is still used by " + std::to_string(L->n_runs.load()) +
                                 " live run(s): free the runs first");
   if (!L->host_only) {
+    scratch_handle_freed();
     (void)hipDeviceSynchronize();
-    scratch_trim();
   }
   free_ligand_device(L);
   delete L;
@@ -1096,11 +1203,22 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
 
 // ================================================================ differentiable form
 
-// Poses from which the adjoint with float atomics takes scratch all the same:
-// with Vina terms 512 poses take 79 us back to back either way (90 and 96
-// after a synchronisation), 2,048 some 250 with every atomic in dL/dG and
-// 110 through the sums, whose passes cost some 40 us.
-constexpr int64_t kSumPoses = 768;
+// Whether an adjoint with float atomics collects dL/dG in sums (scratch for
+// `bytes` of them).  Atomics into dL/dG cost 8 K an atom, the passes of the sums
+// some 40 us a call.  64^3 nodes, ligands of 10-60 atoms, us by atomics and
+// through sums: TRIDS (K = 3) 1,024 poses 90 and 97, 1,280 101 and 103, 1,536
+// 116 and 110; Vina (K = 5) 512 poses 81 and 95, 768 100 and 100, 1,024 117 and
+// 105.  Scratch above the bound is mapped anew after every synchronisation:
+// 192^3 nodes (216 MiB), TRIDS, 2,048 poses 177 and 484.
+constexpr long long kSumWork = 3840;
+static bool sums_pay(int64_t n_poses, int K, size_t bytes) {
+  return n_poses * K >= (bytes <= kScratchKeep ? kSumWork : 8 * kSumWork);
+}
+// Whether it takes dL/dw as per-pose contributions, one more launch instead of
+// K atomics a pose on the same K addresses (which the atomics into dL/dG hide in
+// part).  us by atomics and per pose, with dL/dG: TRIDS 512 poses 63 and 66, 768
+// 85 and 79, Vina 512 85 and 81; without: TRIDS 512 47 and 45, Vina 256 both 42.
+static bool pose_w_pays(int64_t n_poses, int K, bool want_g) { return n_poses * K >= (want_g ? 2304 : 1536); }
 
 static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligands_t L, int64_t n_poses,
                       const int32_t* pose_lig, const float* q, int32_t q_stride, const float* xyz,
@@ -1156,10 +1274,9 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool two = wc.apl == 2;
   // dL/dG through per-pocket sums (see Scatter) and dL/dw through per-pose
-  // contributions: always when they have to be repeatable, else from
-  // kSumPoses poses on, unless the stream is being captured, which would
-  // record the scratch allocations.  Scratch is allocated on the stream and
-  // released after the last kernel that reads it.
+  // contributions: always when they have to be repeatable, else where they pay,
+  // unless the stream is being captured, which would record the scratch
+  // allocations.
   bool want_g = false;
   GridDev grids[kMaxDiffPockets];
   for (int i = 0; i < n_pockets; ++i) {
@@ -1167,28 +1284,27 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
     a.unit_off[i + 1] = a.unit_off[i] + (a.dLdG[i] ? adj_units(grids[i]) : 0);
     want_g |= a.dLdG[i] != nullptr;
   }
-  bool scratch = dLdE && (want_g || dLdw) && (deterministic || n_poses >= kSumPoses);
-  if (scratch && !deterministic) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    scratch = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-  }
-  if (!scratch) {
+  // one allocation: sums, per-pose contributions, then bounds and flags next
+  // to each other (one clear)
+  const long long units = a.unit_off[n_pockets];
+  const auto round16 = [](size_t n) { return (n + 15) / 16 * 16; };
+  const size_t bound_bytes = sizeof(unsigned) * kBoundWords, flag_words = (bound_bytes + size_t(units) + 3) / 4;
+  size_t sum_bytes = size_t(units) * kSumUnit * (deterministic ? K * sizeof(unsigned long long) : sizeof(float));
+  const bool may = dLdE && (deterministic || !capturing(s));
+  const bool sums = may && want_g && (deterministic || sums_pay(n_poses, K, sum_bytes + 4 * flag_words));
+  const bool per_pose_w = may && dLdw && (deterministic || pose_w_pays(n_poses, K, want_g));
+  if (!sums && !per_pose_w) {
     HIP_TRY(launch_terms(a, two, K, s));
     return DOCK_OK;
   }
-  const bool sums = want_g, per_pose_w = dLdw != nullptr;
-  const long long units = a.unit_off[n_pockets];
-  // one allocation: sums, per-pose contributions, then bounds and flags next
-  // to each other (one clear)
-  a.fixed = deterministic ? K : 0;
-  const auto round16 = [](size_t n) { return (n + 15) / 16 * 16; };
-  const size_t sum_bytes =
-      sums ? size_t(units) * kSumUnit * (a.fixed ? K * sizeof(unsigned long long) : sizeof(float)) : 0;
+  sum_bytes = sums ? sum_bytes : 0;
   const size_t wp_bytes = per_pose_w ? round16(sizeof(float) * size_t(n_poses) * K) : 0;
   const size_t wk_bytes = per_pose_w ? round16(sizeof(int) * size_t(n_poses)) : 0;
-  const size_t bound_bytes = sizeof(unsigned) * kBoundWords, flag_words = (bound_bytes + size_t(units) + 3) / 4;
-  unsigned char* mem = nullptr;
-  hipError_t e = scratch_alloc(reinterpret_cast<void**>(&mem), sum_bytes + wp_bytes + wk_bytes + 4 * flag_words, s);
+  const size_t bytes = sum_bytes + wp_bytes + wk_bytes + (sums ? 4 * flag_words : 0);
+  a.fixed = deterministic ? K : 0;
+  Scratch held;
+  hipError_t e = scratch_take(bytes, s, &held);
+  unsigned char* const mem = held.mem;
   if (e != hipSuccess && !deterministic) {
     (void)hipGetLastError();  // no memory for the scratch: float atomics
     a.fixed = 0;
@@ -1228,7 +1344,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
     }
   }
   if (e == hipSuccess && per_pose_w) e = launch_adj_wreduce(a.w_pose, a.w_pocket, n_poses, n_pockets, K, dLdw, s);
-  if (mem) (void)hipFreeAsync(mem, s);
+  scratch_give(held, s);
   if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? DOCK_E_OOM : DOCK_E_HIP, std::string("adjoint: ") + hipGetErrorString(e));
   return DOCK_OK;
@@ -1560,11 +1676,6 @@ static int capture_phase(dock_run_s* r, int steps) {
 }
 
 static bool uses_graph(const dock_run_s* r) { return r->p.use_graph && r->p.form == DOCK_FORM_BATCHED; }
-
-static bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
-}
 
 // A phase of as many steps as the run's graph replays it.  Other phases are
 // launched as they are, and captured when as many steps come a second time in
@@ -2274,17 +2385,15 @@ int dock_pocket_map_adjoint(dock_pocket_t p, const float* dLdG, float* dLdxyz, d
   a.lam = dLdG;
   a.dLdxyz = dLdxyz;
   a.dLdtheta = dLdtheta;
-  // node masks in stream-ordered scratch; a call under capture (which would
-  // record the allocation) or without memory for it does without
+  // node masks in scratch; a call under capture (which would record the
+  // allocation) or without memory for it does without
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (p->n_rec > 0 && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-      scratch_alloc(reinterpret_cast<void**>(&a.mask), size_t(map_adjoint_bricks(a.grid)) * 8, s) != hipSuccess) {
+  Scratch held;
+  if (p->n_rec > 0 && !capturing(s) && scratch_take(size_t(map_adjoint_bricks(a.grid)) * 8, s, &held) != hipSuccess)
     (void)hipGetLastError();
-    a.mask = nullptr;
-  }
+  a.mask = reinterpret_cast<unsigned long long*>(held.mem);
   const hipError_t e = launch_map_adjoint(a, s);
-  if (a.mask) (void)hipFreeAsync(a.mask, s);
+  scratch_give(held, s);
   HIP_TRY(e);
   return DOCK_OK;
 } catch (...) {
