@@ -238,10 +238,11 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
  * All pockets of a call share one preset; n_pockets <= 16.
  *   deterministic  0: by float atomics (summation order, and so the last bits,
  *                     vary from call to call); calls on several streams may
- *                     add to one buffer.  From 1,280 poses (TRIDS terms) or
- *                     768 (Vina) on the contributions are first collected per
- *                     call, outside stream capture and where scratch can be
- *                     had, and dL/dw reduced in a fixed order;
+ *                     add to one buffer.  Larger calls (from 1,408 poses with
+ *                     TRIDS terms, 845 with Vina) first collect their
+ *                     contributions, outside stream capture and where scratch
+ *                     can be had, and reduce dL/dw in a fixed order (from 512
+ *                     and 308);
  *                  1: bitwise repeatable.  dL/dG is summed as 64-bit
  *                     integers: every corner contribution is rounded once to
  *                     a multiple of 2^(e - 62), where 2^e bounds any node's

@@ -1206,19 +1206,18 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
 // Whether an adjoint with float atomics collects dL/dG in sums (scratch for
 // `bytes` of them).  Atomics into dL/dG cost 8 K an atom, the passes of the sums
 // some 40 us a call.  64^3 nodes, ligands of 10-60 atoms, us by atomics and
-// through sums: TRIDS (K = 3) 1,024 poses 90 and 97, 1,280 101 and 103, 1,536
-// 116 and 110; Vina (K = 5) 512 poses 81 and 95, 768 100 and 100, 1,024 117 and
-// 105.  Scratch above the bound is mapped anew after every synchronisation:
-// 192^3 nodes (216 MiB), TRIDS, 2,048 poses 177 and 484.
-constexpr long long kSumWork = 3840;
+// through sums: TRIDS (K = 3) 1,024 poses 77 and 89, 1,280 89 and 95, 1,536 101
+// and 98, 2,048 124 and 109; Vina (K = 5) 512 poses 68 and 92, 768 93 and 96,
+// 1,024 107 and 99.  Scratch above the bound is mapped anew after every
+// synchronisation: 192^3 nodes (216 MiB), TRIDS, 2,048 poses 128 and 330-480.
+constexpr long long kSumWork = 4224;
 static bool sums_pay(int64_t n_poses, int K, size_t bytes) {
   return n_poses * K >= (bytes <= kScratchKeep ? kSumWork : 8 * kSumWork);
 }
 // Whether it takes dL/dw as per-pose contributions, one more launch instead of
-// K atomics a pose on the same K addresses (which the atomics into dL/dG hide in
-// part).  us by atomics and per pose, with dL/dG: TRIDS 512 poses 63 and 66, 768
-// 85 and 79, Vina 512 85 and 81; without: TRIDS 512 47 and 45, Vina 256 both 42.
-static bool pose_w_pays(int64_t n_poses, int K, bool want_g) { return n_poses * K >= (want_g ? 2304 : 1536); }
+// K atomics a pose on the same K addresses: TRIDS 512 poses 61 us either way, 768
+// 78 and 65, Vina 512 84 and 68.
+constexpr long long kPoseWWork = 1536;
 
 static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligands_t L, int64_t n_poses,
                       const int32_t* pose_lig, const float* q, int32_t q_stride, const float* xyz,
@@ -1292,7 +1291,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   size_t sum_bytes = size_t(units) * kSumUnit * (deterministic ? K * sizeof(unsigned long long) : sizeof(float));
   const bool may = dLdE && (deterministic || !capturing(s));
   const bool sums = may && want_g && (deterministic || sums_pay(n_poses, K, sum_bytes + 4 * flag_words));
-  const bool per_pose_w = may && dLdw && (deterministic || pose_w_pays(n_poses, K, want_g));
+  const bool per_pose_w = may && dLdw && (deterministic || n_poses * K >= kPoseWWork);
   if (!sums && !per_pose_w) {
     HIP_TRY(launch_terms(a, two, K, s));
     return DOCK_OK;

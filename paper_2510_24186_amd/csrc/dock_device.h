@@ -411,7 +411,6 @@ DK_INLINE uint32_t mul_u24(uint32_t a, uint32_t b) { return (a & 0xffffffu) * (b
 struct Trilerp {
   float v, gx, gy, gz, eout;
   int base;          // flat index of corner (0,0,0)
-  int cx, cy, cz;    // its cell
   float fx, fy, fz;  // cell fractions
 };
 
@@ -430,6 +429,21 @@ DK_INLINE void cell_axis(float p, float o, float hi, float inv_h, int n, float& 
   f = FUSED ? __builtin_fmaf(pc - o, inv_h, -float(c)) : u - float(c);
 }
 
+// The cell of a point, as trilerp takes it (the same bits).
+struct TrilerpCell {
+  int cx, cy, cz;
+  float fx, fy, fz;
+};
+DK_INLINE TrilerpCell trilerp_cell(const GridDev& g, float px, float py, float pz) {
+  TrilerpCell t;
+  float pc;
+  bool in;
+  cell_axis<false>(px, g.origin[0], g.hi[0], g.inv_spacing, g.dims[0], pc, in, t.cx, t.fx);
+  cell_axis<true>(py, g.origin[1], g.hi[1], g.inv_spacing, g.dims[1], pc, in, t.cy, t.fy);
+  cell_axis<true>(pz, g.origin[2], g.hi[2], g.inv_spacing, g.dims[2], pc, in, t.cz, t.fz);
+  return t;
+}
+
 // M: the maps of one pocket, `first` the float index of the wanted map.
 DK_INLINE Trilerp trilerp(const float* __restrict__ M, uint64_t first, const GridDev& g, float px, float py, float pz) {
   Trilerp t;
@@ -442,9 +456,6 @@ DK_INLINE Trilerp trilerp(const float* __restrict__ M, uint64_t first, const Gri
   // dims <= 1024: rows and nodes from full-rate 24-bit products (a 32-bit
   // integer product takes four times as long), node indices below 2^30
   const uint32_t nx = uint32_t(g.dims[0]), nxy = uint32_t(g.dims[0]) * uint32_t(g.dims[1]);
-  t.cx = cx;
-  t.cy = cy;
-  t.cz = cz;
   t.base = int(mul_u24(mul_u24(uint32_t(cz), uint32_t(g.dims[1])) + uint32_t(cy), nx) + uint32_t(cx));
   const float* p0 = M + (first + uint32_t(t.base));
   const float c000 = ldg(p0), c100 = ldg(p0 + 1), c010 = ldg(p0 + nx), c110 = ldg(p0 + nx + 1);
@@ -1365,26 +1376,85 @@ DK_INLINE void mark_units(unsigned char* flag, const SumGrid& sg, const GridDev&
         flag[size_t(type) * sg.nb + (size_t(z) * sg.nby + y) * sg.nbx + b] = 1;
 }
 
+// Adds dL/dG of one pose's atoms (see Scatter) at the positions that eval_terms
+// left.  The last step of a pose: a wave's loads are waited for in order with
+// its atomics, and those take longest.  (Between the maps' values and the pairs,
+// whose records are loaded: captured call of 2,048 poses, TRIDS terms, all by
+// atomics 169 us, last 159; the deterministic call 179 and 167.)
+template <int APL, int K>
+DK_INLINE void scatter_terms(const LaneLig<APL>& L, const float (&x)[APL][3], const GridDev& grid, const float (&w)[K],
+                             int r, float dLdE, const Scatter& sc) {
+  if (!sc.direct && !sc.sum && !(sc.fixed && sc.scale > 0.0)) return;
+  const size_t nxyz = size_t(grid.dims[0]) * grid.dims[1] * grid.dims[2];
+  const int nx = grid.dims[0], nxy = grid.dims[0] * grid.dims[1];
+  const SumGrid sg = sum_grid(grid);
+#pragma unroll
+  for (int s = 0; s < APL; ++s) {
+    if (APL * r + s >= L.n_atoms) continue;
+    const TrilerpCell t = trilerp_cell(grid, x[s][0], x[s][1], x[s][2]);
+    auto corners = [&](float c, float (&cv)[8]) {
+      const float fx = t.fx, fy = t.fy, fz = t.fz;
+      cv[0] = c * (1.f - fx) * (1.f - fy) * (1.f - fz);
+      cv[1] = c * fx * (1.f - fy) * (1.f - fz);
+      cv[2] = c * (1.f - fx) * fy * (1.f - fz);
+      cv[3] = c * fx * fy * (1.f - fz);
+      cv[4] = c * (1.f - fx) * (1.f - fy) * fz;
+      cv[5] = c * fx * (1.f - fy) * fz;
+      cv[6] = c * (1.f - fx) * fy * fz;
+      cv[7] = c * fx * fy * fz;
+    };
+    if (sc.direct) {
+      const size_t co[8] = {0, 1, size_t(nx), size_t(nx) + 1, size_t(nxy), size_t(nxy) + 1,
+                            size_t(nxy) + nx, size_t(nxy) + nx + 1};
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        float* dst = sc.direct + size_t(L.atype[s] * K + k) * nxyz + (size_t(t.cz) * nxy + size_t(t.cy) * nx + t.cx);
+        float cv[8];
+        corners(dLdE * w[k], cv);
+#pragma unroll
+        for (int cn = 0; cn < 8; ++cn) atomicAdd(dst + co[cn], cv[cn]);
+      }
+      continue;
+    }
+    const int unit = sc.fixed ? K * kSumUnit : kSumUnit;
+    const size_t t0 = size_t(L.atype[s]) * sg.nb * unit;
+    const size_t ox[2] = {t0 + sum_x(unit, t.cx), t0 + sum_x(unit, t.cx + 1)};
+    const size_t oy[2] = {sum_y(sg, unit, t.cy), sum_y(sg, unit, t.cy + 1)};
+    const size_t oz[2] = {sum_z(sg, unit, t.cz), sum_z(sg, unit, t.cz + 1)};
+    float cv[8];
+    if (sc.sum) {
+      corners(dLdE, cv);
+#pragma unroll
+      for (int cn = 0; cn < 8; ++cn) atomicAdd(sc.sum + ox[cn & 1] + oy[cn >> 1 & 1] + oz[cn >> 2], cv[cn]);
+      continue;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      corners(dLdE * w[k], cv);
+#pragma unroll
+      for (int cn = 0; cn < 8; ++cn)
+        atomicAdd(sc.fixed + k * kSumUnit + ox[cn & 1] + oy[cn >> 1 & 1] + oz[cn >> 2],
+                  static_cast<unsigned long long>(__double2ll_rn(double(cv[cn]) * sc.scale)));
+    }
+  }
+}
+
 // Differentiable form: the score over per-term maps G[t][k] with weights w
-// (E = sum_k w_k (sum_i trilerp(G[t_i][k], x_i) + sum_pairs phi_k) + E_out),
-// optionally scattering dL/dG for dL/dE = dLdE (see Scatter; in fixed point
-// every corner contribution is rounded once to an integer multiple of 1 /
-// scale, a power of two).  Intra-pair forces are gathered in
-// a fixed order and summed in FP64 (pass layout) or summed in LDS as 64-bit
-// fixed point scaled from a bound on the pair forces, so they do not depend
-// on timing either.  ADJ: false for the energy alone (no scatter, no
-// forces).  `pairs`: the ligand's records in global memory.  Atom positions
-// come from FK of q (XIN = false) or are given (XIN = true).  Leaves
-// per-atom gradients in g, per-term sums (reduced over the group) in ek, and
-// returns E.
+// (E = sum_k w_k (sum_i trilerp(G[t_i][k], x_i) + sum_pairs phi_k) + E_out).
+// Intra-pair forces are gathered in a fixed order and summed in FP64 (pass
+// layout) or summed in LDS as 64-bit fixed point scaled from a bound on the
+// pair forces, so they do not depend on timing either.  ADJ: false for the
+// energy alone (no forces).  `pairs`: the ligand's records in global memory.
+// Atom positions come from FK of q (XIN = false) or are given (XIN = true).
+// Leaves per-atom gradients in g, per-term sums (reduced over the group) in
+// ek, and returns E.
 template <int LPP, int APL, int K, bool XIN, bool ADJ>
 DK_INLINE float eval_terms(const LaneLig<APL>& L, float q, float (&x)[APL][3], float (&g)[APL][3],
                            Rigid& rg, const float* __restrict__ G, const GridDev& grid,
                            const float (&w)[K], const PairRec* __restrict__ pairs, const GroupSlab& S,
-                           int r, float dLdE, const Scatter& sc, float (&ek)[K]) {
+                           int r, float (&ek)[K]) {
   if (!XIN) rg = fk_place<LPP, APL>(L, q, r, x, S.xs);
   const size_t nxyz = size_t(grid.dims[0]) * grid.dims[1] * grid.dims[2];
-  const int nx = grid.dims[0], nxy = grid.dims[0] * grid.dims[1];
   float el[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) el[k] = 0.f;
@@ -1413,44 +1483,6 @@ DK_INLINE float eval_terms(const LaneLig<APL>& L, float q, float (&x)[APL][3], f
           g[s][0] += sx;
           g[s][1] += sy;
           g[s][2] += sz;
-        }
-        auto corners = [&](float c, float (&cv)[8]) {
-          const float fx = tl.fx, fy = tl.fy, fz = tl.fz;
-          cv[0] = c * (1.f - fx) * (1.f - fy) * (1.f - fz);
-          cv[1] = c * fx * (1.f - fy) * (1.f - fz);
-          cv[2] = c * (1.f - fx) * fy * (1.f - fz);
-          cv[3] = c * fx * fy * (1.f - fz);
-          cv[4] = c * (1.f - fx) * (1.f - fy) * fz;
-          cv[5] = c * fx * (1.f - fy) * fz;
-          cv[6] = c * (1.f - fx) * fy * fz;
-          cv[7] = c * fx * fy * fz;
-        };
-        if (ADJ && sc.direct) {
-          float* dst = sc.direct + size_t(L.atype[s] * K + k) * nxyz + tl.base;
-          float cv[8];
-          corners(dLdE * w[k], cv);
-          const size_t co[8] = {0, 1, size_t(nx), size_t(nx) + 1, size_t(nxy), size_t(nxy) + 1,
-                                size_t(nxy) + nx, size_t(nxy) + nx + 1};
-#pragma unroll
-          for (int cn = 0; cn < 8; ++cn) atomicAdd(dst + co[cn], cv[cn]);
-        }
-        if (ADJ && ((k == 0 && sc.sum) || (sc.fixed && sc.scale > 0.0))) {
-          const SumGrid sg = sum_grid(grid);
-          const int unit = sc.fixed ? K * kSumUnit : kSumUnit;
-          float cv[8];
-          corners(sc.fixed ? dLdE * w[k] : dLdE, cv);
-          const size_t t0 = size_t(L.atype[s]) * sg.nb * unit + k * kSumUnit;
-          const size_t ox[2] = {t0 + sum_x(unit, tl.cx), t0 + sum_x(unit, tl.cx + 1)};
-          const size_t oy[2] = {sum_y(sg, unit, tl.cy), sum_y(sg, unit, tl.cy + 1)};
-          const size_t oz[2] = {sum_z(sg, unit, tl.cz), sum_z(sg, unit, tl.cz + 1)};
-#pragma unroll
-          for (int cn = 0; cn < 8; ++cn) {
-            const size_t at = ox[cn & 1] + oy[cn >> 1 & 1] + oz[cn >> 2];
-            if (sc.fixed)
-              atomicAdd(sc.fixed + at, static_cast<unsigned long long>(__double2ll_rn(double(cv[cn]) * sc.scale)));
-            else
-              atomicAdd(sc.sum + at, cv[cn]);
-          }
         }
       }
       S.xs[atom] = make_float4(x[s][0], x[s][1], x[s][2], 0.f);

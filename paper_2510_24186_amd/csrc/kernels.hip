@@ -692,36 +692,11 @@ DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* s
   } else {
     q = r < lg.n_dof ? a.q[pose * a.q_stride + r] : 0.f;
   }
-  const float dLdE = ADJ ? a.dLdE[pose] : 0.f;
-  Scatter sc;
-  if (ADJ && a.dLdG[pi]) {
-    const size_t at = size_t(a.unit_off[pi]) * kSumUnit;
-    // (float sums are multiplied by w_k afterwards, where the sum is not zero:
-    // a weight that is not finite has to meet every contribution, zeros too)
-    bool finite_w = true;
-#pragma unroll
-    for (int k = 0; k < K; ++k) finite_w &= fabsf(w[k]) <= FLT_MAX;
-    if (!a.sum || (!a.fixed && !finite_w)) {
-      sc.direct = a.dLdG[pi];
-    } else if (a.fixed) {
-      sc.fixed = static_cast<unsigned long long*>(a.sum) + at * K;
-      sc.scale = fixed_scale(a, pi, K);
-    } else {
-      sc.sum = static_cast<float*>(a.sum) + at;
-    }
-  }
   const float E = eval_terms<LPP, APL, K, XIN, ADJ>(L, q, x, g, rg, a.G[pi], pk.grid, w, a.L.pairs + lg.pair_off, S,
-                                                    r, dLdE, sc, ek);
+                                                    r, ek);
   if (r == 0 && a.E) a.E[pose] = E;
   if (!ADJ) return;
-  if (r == 0 && a.w_pose) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) a.w_pose[pose * K + k] = dLdE * ek[k];
-    a.w_pocket[pose] = pi;
-  } else if (r == 0 && a.dLdw) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) atomicAdd(&a.dLdw[pi * K + k], dLdE * ek[k]);
-  }
+  const float dLdE = a.dLdE[pose];
   if (a.dLdx) {
 #pragma unroll
     for (int s = 0; s < APL; ++s) {
@@ -737,6 +712,33 @@ DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* s
   if (!XIN && a.dLdq) {
     const float gq = chain_rule<LPP, APL>(L, rg, x, g, S, r);
     if (r < lg.n_dof) a.dLdq[pose * a.q_stride + r] += dLdE * gq;
+  }
+  // atomics last: loads after them would wait for them
+  if (r == 0 && a.w_pose) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) a.w_pose[pose * K + k] = dLdE * ek[k];
+    a.w_pocket[pose] = pi;
+  } else if (r == 0 && a.dLdw) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) atomicAdd(&a.dLdw[pi * K + k], dLdE * ek[k]);
+  }
+  if (a.dLdG[pi]) {
+    Scatter sc;
+    const size_t at = size_t(a.unit_off[pi]) * kSumUnit;
+    // (float sums are multiplied by w_k afterwards, where the sum is not zero:
+    // a weight that is not finite has to meet every contribution, zeros too)
+    bool finite_w = true;
+#pragma unroll
+    for (int k = 0; k < K; ++k) finite_w &= fabsf(w[k]) <= FLT_MAX;
+    if (!a.sum || (!a.fixed && !finite_w)) {
+      sc.direct = a.dLdG[pi];
+    } else if (a.fixed) {
+      sc.fixed = static_cast<unsigned long long*>(a.sum) + at * K;
+      sc.scale = fixed_scale(a, pi, K);
+    } else {
+      sc.sum = static_cast<float*>(a.sum) + at;
+    }
+    scatter_terms<APL, K>(L, x, pk.grid, w, r, dLdE, sc);
   }
 }
 
