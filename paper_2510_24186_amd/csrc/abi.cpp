@@ -1195,7 +1195,7 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
   a.dEdq = dEdq;
   a.xyz = xyz_out;
   a.xyz_stride = xyz_stride;
-  HIP_TRY(launch_score(a, wc.apl == 2, eval_mode(pockets, n_pockets, L), reinterpret_cast<hipStream_t>(stream)));
+  HIP_TRY(launch_score(a, wc.lpp * wc.apl, eval_mode(pockets, n_pockets, L), reinterpret_cast<hipStream_t>(stream)));
   return DOCK_OK;
 } catch (...) {
   return exception_status();
@@ -1271,7 +1271,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   a.dLdq = dLdq;
   a.dLdx = dLdx;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const bool two = wc.apl == 2;
+  const int lanes = wc.lpp * wc.apl;
   // dL/dG through per-pocket sums (see Scatter) and dL/dw through per-pose
   // contributions: always when they have to be repeatable, else where they pay,
   // unless the stream is being captured, which would record the scratch
@@ -1293,7 +1293,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   const bool sums = may && want_g && (deterministic || sums_pay(n_poses, K, sum_bytes + 4 * flag_words));
   const bool per_pose_w = may && dLdw && (deterministic || n_poses * K >= kPoseWWork);
   if (!sums && !per_pose_w) {
-    HIP_TRY(launch_terms(a, two, K, s));
+    HIP_TRY(launch_terms(a, lanes, K, s));
     return DOCK_OK;
   }
   sum_bytes = sums ? sum_bytes : 0;
@@ -1307,7 +1307,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   if (e != hipSuccess && !deterministic) {
     (void)hipGetLastError();  // no memory for the scratch: float atomics
     a.fixed = 0;
-    HIP_TRY(launch_terms(a, two, K, s));
+    HIP_TRY(launch_terms(a, lanes, K, s));
     return DOCK_OK;
   }
   if (e == hipSuccess) {
@@ -1320,11 +1320,11 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
       a.bound = reinterpret_cast<unsigned*>(mem + sum_bytes + wp_bytes + wk_bytes);
       a.flag = reinterpret_cast<unsigned char*>(a.bound) + bound_bytes;
       e = launch_fill_u32(a.bound, (long long)flag_words, 0u, s);
-      if (e == hipSuccess) e = launch_adj_mark(a, two, s);
+      if (e == hipSuccess) e = launch_adj_mark(a, lanes, s);
       if (e == hipSuccess) e = launch_adj_clear(a, s);
     }
   }
-  if (e == hipSuccess) e = launch_terms(a, two, K, s);
+  if (e == hipSuccess) e = launch_terms(a, lanes, K, s);
   if (sums && e == hipSuccess) {
     // all pockets at once unless two of them share (part of) a buffer
     bool apart = true;

@@ -1469,6 +1469,11 @@ DK_INLINE float eval_terms(const LaneLig<APL>& L, float q, float (&x)[APL][3], f
       for (int k = 0; k < K; ++k) {
         const Trilerp tl = trilerp(base + size_t(k) * nxyz, 0, grid, x[s][0], x[s][1], x[s][2]);
         el[k] += tl.v;
+        // one term's eight corners at a time: with the loads of all terms in
+        // flight, four poses a wave lose the lines that a term's corners share
+        // from L1 (65,536 poses of 10- and 14-atom ligands, Vina terms: kernel
+        // 169 us so, 159 now)
+        if (LPP == 16 && !ADJ) __builtin_amdgcn_sched_barrier(0);
         if (k == 0) eout += tl.eout;  // the out-of-box penalty is the same for every term
         // trilerp() adds the out-of-box slope to its gradient; remove it from
         // every term and add it once below

@@ -79,7 +79,7 @@ struct TermsArgs {
 // The passes around launch_terms when a.sum is set: units marked (flag and
 // bound cleared by the caller), the marked units' sums cleared, and after
 // launch_terms the units [u0, u1) added to dLdG.
-hipError_t launch_adj_mark(TermsArgs a, bool two_per_lane, hipStream_t s);
+hipError_t launch_adj_mark(TermsArgs a, int lanes, hipStream_t s);
 hipError_t launch_adj_clear(const TermsArgs& a, hipStream_t s);
 hipError_t launch_adj_expand(const TermsArgs& a, const GridDev* grids, int K, long long u0, long long u1, hipStream_t s);
 // units of a pocket
@@ -168,8 +168,9 @@ size_t group_lds_bytes(int lpp, int apl, int max_pairs);
 
 hipError_t launch_map_build(const MapArgs& a, hipStream_t s);
 // mode: 0 grid maps, 1 direct pair sums, 2 grid maps + E_MDN
-// (two_per_lane: some ligand of the handle has more than 64 atoms)
-hipError_t launch_score(ScoreArgs a, bool two_per_lane, int mode, hipStream_t s);
+// (lanes: of the handle's widest ligand, 16, 32 or 64; 128 where one has more
+// than 64 atoms, two a lane)
+hipError_t launch_score(ScoreArgs a, int lanes, int mode, hipStream_t s);
 hipError_t launch_sample(const SampleArgs& a, int lpp, int apl, int grid, int block, int mode,
                          hipStream_t s);
 hipError_t launch_best(const BestArgs& a, hipStream_t s);
@@ -189,7 +190,7 @@ struct RankArgs {
   int* out_idx;
 };
 hipError_t launch_rank(const RankArgs& a, hipStream_t s);
-hipError_t launch_terms(TermsArgs a, bool two_per_lane, int K, hipStream_t s);
+hipError_t launch_terms(TermsArgs a, int lanes, int K, hipStream_t s);
 hipError_t launch_philox(const uint32_t* ctr, uint32_t k0, uint32_t k1, long long n, uint32_t* out,
                          hipStream_t s);
 hipError_t launch_fill_int(int* p, int n, int v, hipStream_t s);

@@ -539,12 +539,12 @@ DK_INLINE int lane_config(const LigDev* g) {
   return need <= 16 ? 16 : (need <= 32 ? 32 : 64);
 }
 // slabs of the forms: 4 of 16 lanes, 2 of 32, 1 of 64
-constexpr size_t wave_slab_bytes(bool two_per_lane) {
-  return two_per_lane ? slab_bytes(64, 2)
+constexpr size_t wave_slab_bytes(int lanes) {
+  return lanes == 128 ? slab_bytes(64, 2)
                       : std::max({4 * slab_bytes(16, 1), 2 * slab_bytes(32, 1), slab_bytes(64, 1)});
 }
 constexpr size_t kClashBytes = sizeof(float) * kClashTable;
-size_t wave_lds_bytes(bool two_per_lane) { return wave_slab_bytes(two_per_lane) + 4 * kClashBytes; }
+size_t wave_lds_bytes(int lanes) { return wave_slab_bytes(lanes) + 4 * kClashBytes; }
 
 // The log2(d_clash) table of a pass layout into the group's LDS.
 template <int LPP>
@@ -596,11 +596,19 @@ DK_INLINE void score_poses(const ScoreArgs& a, long long first, unsigned char* s
   }
 }
 
-template <int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) score_kernel(ScoreArgs a) {
+// SMALL: every ligand of the handle takes 16 lanes, so a wavefront always takes
+// four poses of one form, with the registers of that form alone (10- and 14-atom
+// ligands, 8,192 poses: kernel 15.8 us in the general form, 9.3 so; 65,536 51.3 and
+// 40.1).
+template <int MODE, bool SMALL>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SMALL ? 4 : 3))) score_kernel(ScoreArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* tables = smem + a.slab_bytes;
   const long long base = (long long)blockIdx.x * a.chunk;
+  if (SMALL) {
+    score_poses<16, 1, MODE>(a, base, smem, tables);
+    return;
+  }
   const int n = int(min((long long)a.chunk, a.n_poses - base));
   int cfg = 0;
   if (int(threadIdx.x) < n) {
@@ -622,24 +630,32 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) sc
   }
 }
 
-// Poses per wavefront: one until the waves of one pose each would fill the
-// chip's wave slots (4 waves on each of the 1,024 SIMDs), then two, then four
-// (small ligands then share a wave).
-int wave_chunk(long long n_poses) { return n_poses <= 4096 ? 1 : (n_poses <= 8192 ? 2 : 4); }
+// Poses per wavefront, for a handle whose widest ligand takes `lanes` (16, 32,
+// 64; 128: two atoms per lane): one while the waves of one pose each are few,
+// then two, then four where small ligands can share a wave.  Score kernel, us
+// with one and two poses a wave: ligands of 20 and 30 atoms, 2,048 poses 10.9 and
+// 11.4, 4,096 19.5 and 12.2; 10-60 atoms, 4,096 poses 28.2 and 29.2.
+int wave_chunk(long long n_poses, int lanes) {
+  if (lanes == 16) return 4;
+  return n_poses <= (lanes == 32 ? 2048 : 4096) ? 1 : (n_poses <= 8192 ? 2 : 4);
+}
 
-hipError_t launch_score(ScoreArgs a, bool two_per_lane, int mode, hipStream_t s) {
+hipError_t launch_score(ScoreArgs a, int lanes, int mode, hipStream_t s) {
   if (a.n_poses <= 0) return hipSuccess;
-  a.chunk = wave_chunk(a.n_poses);
-  a.slab_bytes = unsigned(wave_slab_bytes(two_per_lane));
+  a.chunk = wave_chunk(a.n_poses, lanes);
+  a.slab_bytes = unsigned(wave_slab_bytes(lanes));
   const unsigned blocks = unsigned((a.n_poses + a.chunk - 1) / a.chunk);
-  const size_t lds = wave_lds_bytes(two_per_lane);
-  if (mode == kModeDirect)
-    hipLaunchKernelGGL(score_kernel<kModeDirect>, dim3(blocks), dim3(64), lds, s, a);
-  else if (mode == kModeGridMdn)
-    hipLaunchKernelGGL(score_kernel<kModeGridMdn>, dim3(blocks), dim3(64), lds, s, a);
-  else
-    hipLaunchKernelGGL(score_kernel<kModeGrid>, dim3(blocks), dim3(64), lds, s, a);
-  return hipGetLastError();
+  const size_t lds = wave_lds_bytes(lanes);
+  const bool small = lanes == 16;
+#define X(M, SM)                                                                      \
+  if (mode == M && small == SM) {                                                     \
+    hipLaunchKernelGGL((score_kernel<M, SM>), dim3(blocks), dim3(64), lds, s, a);     \
+    return hipGetLastError();                                                         \
+  }
+  X(kModeGrid, false) X(kModeGrid, true) X(kModeDirect, false) X(kModeDirect, true)
+  X(kModeGridMdn, false) X(kModeGridMdn, true)
+#undef X
+  return hipErrorInvalidValue;
 }
 
 // ================================================================ differentiable form
@@ -748,14 +764,18 @@ DK_INLINE void terms_poses(const TermsArgs& a, long long first, unsigned char* s
   }
 }
 
-// The adjoint holds two waves per SIMD without spills (three spill 49
-// registers: 16 pockets x 4,096 poses 534 us the call, two 521); the energy
-// alone four.  The gathers from the per-term maps and the scatter's lines,
-// both beyond L2, bound them.
-template <int K, bool XIN, bool ADJ>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ADJ ? 2 : 4))) terms_kernel(TermsArgs a) {
+// The general adjoint holds two waves per SIMD without spills (at three it spills
+// 18 to 28 registers: 8,192 poses of 10-60 atoms, TRIDS, sums 229 us the call, two
+// 219), the others four.  The gathers from the per-term maps and the scatter's
+// lines, both beyond L2, bound them.
+template <int K, bool XIN, bool ADJ, bool SMALL>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ADJ && !SMALL ? 2 : 4))) terms_kernel(TermsArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const long long base = (long long)blockIdx.x * a.chunk;
+  if (SMALL) {  // as in score_kernel
+    terms_poses<16, 1, K, XIN, ADJ>(a, base, smem);
+    return;
+  }
   const int n = int(min((long long)a.chunk, a.n_poses - base));
   int cfg = 0;
   if (int(threadIdx.x) < n) {
@@ -777,19 +797,20 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ADJ ? 2
   }
 }
 
-hipError_t launch_terms(TermsArgs a, bool two_per_lane, int K, hipStream_t s) {
+hipError_t launch_terms(TermsArgs a, int lanes, int K, hipStream_t s) {
   if (a.n_poses <= 0) return hipSuccess;
-  a.chunk = wave_chunk(a.n_poses);
+  a.chunk = wave_chunk(a.n_poses, lanes);
   const unsigned blocks = unsigned((a.n_poses + a.chunk - 1) / a.chunk);
-  const size_t lds = wave_slab_bytes(two_per_lane);
-  const bool xin = a.xyz != nullptr, adj = a.dLdE != nullptr;
-#define X(KK, XI, AD)                                                                              \
-  if (K == KK && xin == XI && adj == AD) {                                                         \
-    hipLaunchKernelGGL((terms_kernel<KK, XI, AD>), dim3(blocks), dim3(64), lds, s, a);             \
+  const size_t lds = wave_slab_bytes(lanes);
+  const bool xin = a.xyz != nullptr, adj = a.dLdE != nullptr, small = lanes == 16;
+#define X(KK, XI, AD, SM)                                                                          \
+  if (K == KK && xin == XI && adj == AD && small == SM) {                                          \
+    hipLaunchKernelGGL((terms_kernel<KK, XI, AD, SM>), dim3(blocks), dim3(64), lds, s, a);         \
     return hipGetLastError();                                                                      \
   }
-  X(3, false, false) X(3, false, true) X(3, true, false) X(3, true, true)
-  X(5, false, false) X(5, false, true) X(5, true, false) X(5, true, true)
+#define Y(KK, XI) X(KK, XI, false, false) X(KK, XI, false, true) X(KK, XI, true, false) X(KK, XI, true, true)
+  Y(3, false) Y(3, true) Y(5, false) Y(5, true)
+#undef Y
 #undef X
   return hipErrorInvalidValue;
 }
@@ -873,11 +894,11 @@ __global__ void __launch_bounds__(64) adj_mark_kernel(TermsArgs a) {
   }
 }
 
-hipError_t launch_adj_mark(TermsArgs a, bool two_per_lane, hipStream_t s) {
+hipError_t launch_adj_mark(TermsArgs a, int lanes, hipStream_t s) {
   if (a.n_poses <= 0) return hipSuccess;
-  a.chunk = wave_chunk(a.n_poses);
+  a.chunk = wave_chunk(a.n_poses, lanes);
   const unsigned blocks = unsigned((a.n_poses + a.chunk - 1) / a.chunk);
-  const size_t lds = wave_slab_bytes(two_per_lane);
+  const size_t lds = wave_slab_bytes(lanes);
   if (a.xyz)
     hipLaunchKernelGGL(adj_mark_kernel<true>, dim3(blocks), dim3(64), lds, s, a);
   else
