@@ -291,7 +291,7 @@ typedef struct {
   uint32_t seed;
   int32_t form;             /* DOCK_FORM_PLAIN: one launch per ligand;
                                DOCK_FORM_BATCHED: ragged-packed persistent launches */
-  int32_t use_graph;        /* batched: replay the launch sequence as a hipGraph */
+  int32_t use_graph;        /* batched: replay a launch sequence that comes again as a hipGraph */
   int32_t steps_per_launch; /* 0: all steps in one launch per bucket */
   int32_t record_trace;     /* store q, E, dE/dq of every evaluation (tests) */
   int32_t lanes_per_pose;   /* 0: planner choice; else 16, 32 or 64: a wider group
@@ -316,11 +316,10 @@ void dock_sample_params_default(dock_sample_params* p);
  * streams forked from `stream` and joined back into it.  The library keeps
  * a pool of side streams per device for the life of the process, shared by
  * all runs.  Runs are created, advanced, restarted and freed from one host
- * thread at a time: with use_graph = 1 (the default) dock_sample launches its
- * MC steps and then captures the same launches as a graph, through the shared
- * side streams, which dock_run_restart replays (a dock_run_advance of another
- * step count is captured when it comes twice in a row), and runs used from
- * several threads at once are not supported.  On a stream that is being
+ * thread at a time: with use_graph = 1 (the default) an MC-step phase of as
+ * many steps as the one before it is captured as a graph through the shared
+ * side streams (a run that is advanced once captures none), and runs used
+ * from several threads at once are not supported.  On a stream that is being
  * captured, restarts and advances enqueue their kernels themselves.
  * A run's ligands of 33-64 atoms are laid out two atoms per lane when its
  * trajectories of such ligands fill at least two waves per wave slot of the
@@ -358,7 +357,9 @@ int dock_run_advance(dock_run_t r, int32_t n_steps, void* stream);
  * pose and takes the run's n_steps MC steps again, in the run's own buffers
  * with its plan and launches, exactly as dock_sample with that seed would.
  * Enqueues kernels only (no allocation, no host synchronisation, no memset):
- * repeated docking of the same ligand set without per-call setup. */
+ * repeated docking of the same ligand set without per-call setup.  (With
+ * use_graph = 1 a run's first restart also makes the graph that the later ones
+ * replay, unless `stream` is being captured; with 0 none does.) */
 int dock_run_restart(dock_run_t r, uint32_t seed, void* stream);
 
 typedef struct {

@@ -1437,7 +1437,6 @@ struct dock_run_s {
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
   int graph_steps = -1;             // steps of the captured graph
-  bool graph_launched = false;
   int eager_steps = -1;             // steps of the last phase launched without one
   // per-launch timing of the last call (eager launches only)
   struct Launch {
@@ -1650,7 +1649,6 @@ static void drop_graph(dock_run_s* r) {
   r->gexec = nullptr;
   r->graph = nullptr;
   r->graph_steps = -1;
-  r->graph_launched = false;
 }
 
 // Captures the launches of a phase of `steps` MC steps as the run's graph.
@@ -1678,9 +1676,11 @@ static bool uses_graph(const dock_run_s* r) { return r->p.use_graph && r->p.form
 
 // A phase of as many steps as the run's graph replays it.  Other phases are
 // launched as they are, and captured when as many steps come a second time in
-// a row: the capture costs more than the launches it replaces.  (dock_sample
-// captures its own phase after launching it.)  On a stream that is being
-// captured the launches themselves go into the caller's graph.
+// a row: a capture costs the host more than the launches (one new run of eight
+// ligands of 10-60 atoms, 64 trajectories x 3 steps: 402 us, 446 with a capture
+// after its launches, 613 with one before them; a restart of one step 234 us as
+// it is, 203 as a graph).  On a stream that is being captured the launches
+// themselves go into the caller's graph.
 static int run_phase(dock_run_s* r, bool init, int steps, hipStream_t s) {
   if (!init && steps == 0) return DOCK_OK;
   if (!init && uses_graph(r) && !capturing(s) && (r->graph_steps == steps || r->eager_steps == steps)) {
@@ -1689,7 +1689,6 @@ static int run_phase(dock_run_s* r, bool init, int steps, hipStream_t s) {
       if (rc != DOCK_OK) return rc;
     }
     HIP_TRY(hipGraphLaunch(r->gexec, s));
-    r->graph_launched = true;
   } else {
     const bool rec = r->recording;
     r->recording = rec && (init || !uses_graph(r));
@@ -1986,8 +1985,8 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   r->n_queue = int(r->buckets.size()) * std::max(1, (p->n_steps + chunk - 1) / chunk) * r->n_part;
   // one allocation: what starts as zeros, the energies and queue (written
   // before they are read), then what is uploaded.  With an allocation, a
-  // clear and a copy for each of these, and a graph captured before the first
-  // launches, a new run of 1,024 trajectories of a 35-atom ligand, 8 steps,
+  // clear and a copy for each of these, and a graph captured for a phase that
+  // ran once, a new run of 1,024 trajectories of a 35-atom ligand, 8 steps,
   // took 575 us with its best poses, of which the host some 200; now 491.
   size_t bytes = 0;
   const auto part = [&](size_t n) {
@@ -2042,8 +2041,6 @@ static int create_run(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   }
   if (e != hipSuccess) return bail(DOCK_E_HIP, std::string("init: ") + hipGetErrorString(e));
   rc = timed_phases(r, true, p->n_steps, s);
-  // the graph that dock_run_restart replays, made while the device works
-  if (rc == DOCK_OK && uses_graph(r) && p->n_steps > 0 && !capturing(s)) rc = capture_phase(r, p->n_steps);
   if (rc != DOCK_OK) {
     std::string m = g_err;
     free_run(r);
@@ -2199,8 +2196,8 @@ int dock_run_restart(dock_run_t r, uint32_t seed, void* stream) try {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const size_t nt = size_t(r->n_lig) * r->T;
   // counters and the trace back to their initial values with fill kernels
-  // rather than memsets (the call enqueues kernels only and allocates
-  // nothing)
+  // rather than memsets (the call enqueues kernels only, but for the graph
+  // that a run's first restart makes)
   HIP_TRY(launch_fill_int(r->n_evals, int(nt), 0, s));
   HIP_TRY(launch_fill_int(r->d_step, 1, 0, s));
   HIP_TRY(launch_fill_int(r->d_step + 1, 1, int(seed), s));
@@ -2319,7 +2316,6 @@ int dock_run_plan(dock_run_t r, int32_t* lig_bucket, int32_t* bucket_lanes, int3
 
 int dock_free_run(dock_run_t r) try {
   if (!r) return DOCK_OK;
-  if (!r->graph_launched) drop_graph(r);  // on the host alone, while the device works
   (void)hipDeviceSynchronize();
   free_run(r);
   return DOCK_OK;
