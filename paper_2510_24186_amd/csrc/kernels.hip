@@ -1560,11 +1560,11 @@ hipError_t launch_best(const BestArgs& a, hipStream_t s) {
   // 14.7, 2,048 32.0 and 30.0, 4,096 47.0 and 50.3; best 24 of 4,096 (six
   // ligands a CU by their LDS) 332 and 167; best 1 of 1,024 8.3 and 11.9, of
   // 4,096 11.0 and 30.9; 256 candidates, best 1: 512 ligands 14.0 and 13.3,
-  // 2,048 16.1 and 25.3.
+  // 2,048 16.1 and 25.3.  (No more poses are kept than there are candidates.)
   constexpr int kCus = 256;
   const int resident = int(std::min<size_t>((size_t(a.n_ligands) + kCus - 1) / kCus, 160 * 1024 / lds(1)));
-  const bool four = (a.top_n >= std::max(4, resident)) || (a.top_n >= 2 && resident <= 1) ||
-                    (a.n_traj >= 256 && resident <= 2);
+  const int keep = std::min(a.top_n, a.n_traj);
+  const bool four = keep >= std::max(4, resident) || (keep >= 2 && resident <= 1) || (a.n_traj >= 256 && resident <= 2);
   if (four && lds(4) <= 64 * 1024)
     hipLaunchKernelGGL(best_kernel<4>, dim3(a.n_ligands), dim3(256), lds(4), s, a);
   else
