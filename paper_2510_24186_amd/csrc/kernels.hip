@@ -71,14 +71,12 @@ __global__ void __launch_bounds__(256) map_kernel(MapArgs a) {
   }
   const int nx = a.grid.dims[0], ny = a.grid.dims[1], nz = a.grid.dims[2];
   const int nbx = (nx + kBrickX - 1) / kBrickX, nby = (ny + kBrickY - 1) / kBrickY;
-  // the bricks of a row along x go to one XCD (blocks go round the eight): they
-  // write 32-byte parts of the same lines, which its L2 then joins (five atoms,
-  // TRIDS with per-term maps, all stores: 192^3 nodes 764 -> 208 us; 800 atoms
-  // 657 -> 545, 128^3 733 -> 456)
-  const int nbz = (nz + kBrickZ - 1) / kBrickZ, local = blockIdx.x / kXcds;
-  const int row = local / nbx * kXcds + blockIdx.x % kXcds;
-  if (row >= nby * nbz) return;
-  const int x0 = (local % nbx) * kBrickX, y0 = (row % nby) * kBrickY, z0 = (row / nby) * kBrickZ;
+  // the row along x and the brick in it (blocks go round the XCDs, see
+  // launch_map_build)
+  const int b = blockIdx.x, local = b / kXcds;
+  const int row = a.rows_on_xcds ? local / nbx * kXcds + b % kXcds : b / nbx, bx = (a.rows_on_xcds ? local : b) % nbx;
+  if (row >= nby * ((nz + kBrickZ - 1) / kBrickZ)) return;
+  const int x0 = bx * kBrickX, y0 = (row % nby) * kBrickY, z0 = (row / nby) * kBrickZ;
   const int ix = x0 + tid % kBrickX, iy = y0 + tid / kBrickX % kBrickY, iz = z0 + wv;
   const bool live = ix < nx && iy < ny && iz < nz;
   // node coordinate: FP64 origin + spacing * index, rounded once to FP32
@@ -209,10 +207,19 @@ __global__ void __launch_bounds__(256) map_kernel(MapArgs a) {
   }
 }
 
-hipError_t launch_map_build(const MapArgs& a, hipStream_t s) {
+// Bricks write 32-byte parts of a line, four bricks along x share it, and blocks
+// go round the eight XCDs: their L2s then write the parts back one by one.  On
+// large grids a row of bricks stays on one XCD; on small ones that leaves the
+// XCDs uneven work (88^3 nodes, 1,210 atoms, Vina terms: 3 % slower by rows).
+// TRIDS with per-term maps, 800 atoms, us brick by brick and row by row: 96^3
+// nodes 420 and 430, 112^3 474 and 455, 128^3 735 and 483, 192^3 786 and 568 (five
+// atoms 1,010 and 271).
+hipError_t launch_map_build(MapArgs a, hipStream_t s) {
   const auto bricks = [](int n, int b) { return unsigned((n + b - 1) / b); };
-  const unsigned rows = bricks(a.grid.dims[1], kBrickY) * bricks(a.grid.dims[2], kBrickZ);
-  const unsigned blocks = bricks(a.grid.dims[0], kBrickX) * ((rows + kXcds - 1) / kXcds * kXcds);
+  const unsigned nbx = bricks(a.grid.dims[0], kBrickX),
+                 rows = bricks(a.grid.dims[1], kBrickY) * bricks(a.grid.dims[2], kBrickZ);
+  a.rows_on_xcds = rows >= 384;
+  const unsigned blocks = nbx * (a.rows_on_xcds ? (rows + kXcds - 1) / kXcds * kXcds : rows);
   if (a.n_terms == 3)
     hipLaunchKernelGGL(map_kernel<3>, dim3(blocks), dim3(256), 0, s, a);
   else
