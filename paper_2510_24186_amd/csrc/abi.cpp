@@ -1181,7 +1181,7 @@ int dock_score_grad(const dock_pocket_t* pockets, int32_t n_pockets, dock_ligand
   if (rc) return rc;
   const LaneCfg wc = wide_cfg(L);
   if (group_lds_bytes(wc.lpp, wc.apl, L->max_alt_pairs) > 64 * 1024)
-    return fail(DOCK_E_LIMIT, "pair list too long for the LDS budget");
+    return fail(DOCK_E_LIMIT, "pair list too long: the groups of a wavefront exceed 64 KiB with their pair records");
   ScoreArgs a{};
   a.L = L->arrays();
   a.pockets = tab;
@@ -1253,7 +1253,7 @@ static int terms_call(const dock_pocket_t* pockets, int32_t n_pockets, dock_liga
   }
   const LaneCfg wc = wide_cfg(L);
   if (group_lds_bytes(wc.lpp, wc.apl, L->max_alt_pairs) > 64 * 1024)
-    return fail(DOCK_E_LIMIT, "pair list too long for the LDS budget");
+    return fail(DOCK_E_LIMIT, "pair list too long: the groups of a wavefront exceed 64 KiB with their pair records");
   a.L = L->arrays();
   a.pockets = tab;
   a.n_ligands = L->n;

@@ -10,7 +10,8 @@
 //  best_kernel    per ligand: bitonic sort of the trajectories' best
 //                 energies, greedy RMSD clustering, top N
 //  rank_kernel    screening rank across ligands: blocks of 2,048 scores
-//                 sorted in LDS and cut to the k smallest, pass by pass
+//                 sorted (two keys a thread, exchanged by shuffles and through
+//                 LDS) and cut to the k smallest, pass by pass
 #include <float.h>
 #include <math.h>
 
@@ -1568,10 +1569,13 @@ hipError_t launch_best(const BestArgs& a, hipStream_t s) {
   // ligands a CU by their LDS) 332 and 167; best 1 of 1,024 8.3 and 11.9, of
   // 4,096 11.0 and 30.9; 256 candidates, best 1: 512 ligands 14.0 and 13.3,
   // 2,048 16.1 and 25.3.  (No more poses are kept than there are candidates.)
+  // Best 8 of 4,096 ligands x 64 candidates of which many are near each other,
+  // with its rank: 174 and 168 us the calls; 16,384 x 16: 220 and 246.
   constexpr int kCus = 256;
   const int resident = int(std::min<size_t>((size_t(a.n_ligands) + kCus - 1) / kCus, 160 * 1024 / lds(1)));
   const int keep = std::min(a.top_n, a.n_traj);
-  const bool four = keep >= std::max(4, resident) || (keep >= 2 && resident <= 1) || (a.n_traj >= 256 && resident <= 2);
+  const bool four = keep >= std::max(4, resident) || (keep >= 8 && a.n_ligands <= 16 * kCus) ||
+                    (keep >= 2 && resident <= 1) || (a.n_traj >= 256 && resident <= 2);
   if (four && lds(4) <= 64 * 1024)
     hipLaunchKernelGGL(best_kernel<4>, dim3(a.n_ligands), dim3(256), lds(4), s, a);
   else
