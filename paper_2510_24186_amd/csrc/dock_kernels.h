@@ -142,7 +142,6 @@ struct MapArgs {
   TypePair tab[kTypes * kTypes];
   float* G;  // [8][K][nodes] or null
   float* M;  // [8][nodes]
-  bool rows_on_xcds;  // set by the launch
 };
 
 // Adjoint of the TRIDS map build: dL/d(receptor xyz) and dL/dtheta for
@@ -167,7 +166,7 @@ size_t sample_lds_bytes(int lpp, int apl, int block, int max_pairs);
 // LDS of the groups of one wavefront with their pair records.
 size_t group_lds_bytes(int lpp, int apl, int max_pairs);
 
-hipError_t launch_map_build(MapArgs a, hipStream_t s);
+hipError_t launch_map_build(const MapArgs& a, hipStream_t s);
 // mode: 0 grid maps, 1 direct pair sums, 2 grid maps + E_MDN
 // (lanes: of the handle's widest ligand, 16, 32 or 64; 128 where one has more
 // than 64 atoms, two a lane)

@@ -49,7 +49,7 @@ __device__ __forceinline__ float d2_rounded(float dx, float dy, float dz) {
 // evaluating each type's terms (same bits).
 constexpr int kBrickX = 8, kBrickY = 8, kBrickZ = 4, kMapList = 512, kXcds = 8;
 
-template <int K>
+template <int K, bool ROWS>
 __global__ void __launch_bounds__(256) map_kernel(MapArgs a) {
   constexpr bool TRIDS = K == 3;
   __shared__ float4 list[kMapList];
@@ -72,12 +72,12 @@ __global__ void __launch_bounds__(256) map_kernel(MapArgs a) {
   }
   const int nx = a.grid.dims[0], ny = a.grid.dims[1], nz = a.grid.dims[2];
   const int nbx = (nx + kBrickX - 1) / kBrickX, nby = (ny + kBrickY - 1) / kBrickY;
-  // the row along x and the brick in it (blocks go round the XCDs, see
-  // launch_map_build)
-  const int b = blockIdx.x, local = b / kXcds;
-  const int row = a.rows_on_xcds ? local / nbx * kXcds + b % kXcds : b / nbx, bx = (a.rows_on_xcds ? local : b) % nbx;
-  if (row >= nby * ((nz + kBrickZ - 1) / kBrickZ)) return;
-  const int x0 = bx * kBrickX, y0 = (row % nby) * kBrickY, z0 = (row / nby) * kBrickZ;
+  int b = blockIdx.x;
+  if (ROWS) {  // see launch_map_build
+    b = (b / kXcds / nbx * kXcds + b % kXcds) * nbx + b / kXcds % nbx;
+    if (b >= nbx * nby * ((nz + kBrickZ - 1) / kBrickZ)) return;
+  }
+  const int x0 = (b % nbx) * kBrickX, y0 = (b / nbx % nby) * kBrickY, z0 = (b / (nbx * nby)) * kBrickZ;
   const int ix = x0 + tid % kBrickX, iy = y0 + tid / kBrickX % kBrickY, iz = z0 + wv;
   const bool live = ix < nx && iy < ny && iz < nz;
   // node coordinate: FP64 origin + spacing * index, rounded once to FP32
@@ -215,16 +215,20 @@ __global__ void __launch_bounds__(256) map_kernel(MapArgs a) {
 // TRIDS with per-term maps, 800 atoms, us brick by brick and row by row: 96^3
 // nodes 420 and 430, 112^3 474 and 455, 128^3 735 and 483, 192^3 786 and 568 (five
 // atoms 1,010 and 271).
-hipError_t launch_map_build(MapArgs a, hipStream_t s) {
+hipError_t launch_map_build(const MapArgs& a, hipStream_t s) {
   const auto bricks = [](int n, int b) { return unsigned((n + b - 1) / b); };
   const unsigned nbx = bricks(a.grid.dims[0], kBrickX),
                  rows = bricks(a.grid.dims[1], kBrickY) * bricks(a.grid.dims[2], kBrickZ);
-  a.rows_on_xcds = rows >= 384;
-  const unsigned blocks = nbx * (a.rows_on_xcds ? (rows + kXcds - 1) / kXcds * kXcds : rows);
-  if (a.n_terms == 3)
-    hipLaunchKernelGGL(map_kernel<3>, dim3(blocks), dim3(256), 0, s, a);
+  const bool by_rows = rows >= 384;
+  const unsigned blocks = nbx * (by_rows ? (rows + kXcds - 1) / kXcds * kXcds : rows);
+  if (a.n_terms == 3 && by_rows)
+    hipLaunchKernelGGL((map_kernel<3, true>), dim3(blocks), dim3(256), 0, s, a);
+  else if (a.n_terms == 3)
+    hipLaunchKernelGGL((map_kernel<3, false>), dim3(blocks), dim3(256), 0, s, a);
+  else if (by_rows)
+    hipLaunchKernelGGL((map_kernel<5, true>), dim3(blocks), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(map_kernel<5>, dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((map_kernel<5, false>), dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
