@@ -105,10 +105,10 @@ def trace_summaries(runs, out):
     terms = [(short(n), g, dur / 1e6) for n, g, wg, dur, lds, scr, st in rows if "terms_kernel" in n or "adj_" in n]
     tl = ["# Kernel trace: the differentiable form (terms_kernel and the deterministic adjoint's helpers)", "",
           "From the same rocprofv3 run as sample_kernel_mixed16_trace.md:", "", "    " + CMD_TRACE, "",
-          "* `terms_kernel<3, false, true>`: the adjoint over the 65,536 best poses of the mixed-pocket step "
+          "* `terms_kernel<3, false, true, false>`: the adjoint over the 65,536 best poses of the mixed-pocket step "
           "(TRIDS,", "  16 pockets, deterministic: 64-bit fixed-point dL/dG), between `adj_mark_kernel` and "
           "`adj_expand_kernel`.",
-          "* `terms_kernel<5, false, false>` and `<5, false, true>`: the differentiation workload (2,048 poses, "
+          "* `terms_kernel<5, false, false, false>` and `<5, false, true, false>`: the differentiation workload (2,048 poses, "
           "Vina-form", "  terms, 64^3 x 8 x 5 maps): forward, adjoint, adjoint deterministic, twice.", "",
           "| Kernel | Grid (threads) | Duration ms |", "|---|---|---|"]
     for k, g, d in terms:
